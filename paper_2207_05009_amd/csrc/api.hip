@@ -17,6 +17,7 @@ struct lq_octree {
     int32_t *d_child;
     int32_t *d_child_skip;
     int32_t *d_top;   // grids of child and child_skip, or null (depth <= kTopLevel)
+    uint32_t *d_bricks;   // brick tables of child_skip
     void *d_rows;
     int64_t bytes;
 };
@@ -255,11 +256,13 @@ lq_status lq_load_octree_desc(const lq_octree_desc *desc, int storage, int devic
     t->d_child = nullptr;
     t->d_child_skip = nullptr;
     t->d_top = nullptr;
+    t->d_bricks = nullptr;
     t->d_rows = nullptr;
     auto release = [&]() {
         (void)hipFree(t->d_child);
         (void)hipFree(t->d_child_skip);
         (void)hipFree(t->d_top);
+        (void)hipFree(t->d_bricks);
         (void)hipFree(t->d_rows);
         delete t;
     };
@@ -279,8 +282,16 @@ lq_status lq_load_octree_desc(const lq_octree_desc *desc, int storage, int devic
         release();
         return hip_fail(e, "uploading the tree");
     }
-    t->bytes = (int64_t)(child_bytes + skip_bytes + top_bytes + row_total);
     DevTree &dt = t->t;
+    size_t brick_bytes = 0;
+    e = build_bricks(t->d_child_skip, desc->max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        release();
+        return e == hipErrorOutOfMemory ? fail(LQ_ERR_OOM, "device allocation of the brick tables failed")
+                                        : hip_fail(e, "building the brick tables");
+    }
+    t->bytes = (int64_t)(child_bytes + skip_bytes + top_bytes + brick_bytes + row_total);
     dt.child = t->d_child;
     dt.child_skip = t->d_child_skip;
     dt.top = top_bytes ? t->d_top : nullptr;
@@ -356,6 +367,7 @@ void lq_free_octree(lq_octree *t) {
     (void)hipFree(t->d_child);
     (void)hipFree(t->d_child_skip);
     (void)hipFree(t->d_top);
+    (void)hipFree(t->d_bricks);
     (void)hipFree(t->d_rows);
     (void)hipSetDevice(cur);
     delete t;

@@ -29,11 +29,34 @@ namespace lq {
 constexpr int kTopLevel = 4;
 constexpr int kTopCells = 1 << (3 * kTopLevel);
 
+// Brick tables of child_skip, marched by the plain query: finest cells in
+// bricks of 8^3 (kBrickBits bits per axis), over a dense grid of
+// (2^brick_top_bits(depth))^3 bricks.
+//  brick_top[z][y][x]: kBrickFull | index of the brick in `bricks`, or, where
+//         the brick holds no leaf, its empty extents;
+//  bricks[brick][z & 7][y & 7][x & 7]: kBrickFull | leaf index, or the empty
+//         extents of an empty cell.
+// Empty extents: for each of the 8 ray octants f (bit a of f set: the ray
+// moves down along axis a) the code in bits 3f..3f+2 is the largest size m of
+// {1, 2, 3, 4, 6, 8, 12, 16} (brick_extent) such that the cube of m cells
+// (brick_top: m bricks) that starts at the cell and reaches along the
+// octant's directions holds no leaf; cells outside the grid count as empty.
+// One entry thus says, for the cell a ray is in, either which leaf it is or
+// how far the ray may go at once, in place of a descent from node to node.
+constexpr int kBrickBits = 3;
+constexpr int kBrickCells = 1 << (3 * kBrickBits);
+constexpr uint32_t kBrickFull = 0x80000000u;
+__host__ __device__ inline int brick_top_bits(int depth) { return depth > kBrickBits ? depth - kBrickBits : 0; }
+// size of an extent code: 1, 2, 3, 4, 6, 8, 12, 16
+__host__ __device__ constexpr int brick_extent(int code) { return ((2 | ((code + 1) & 1)) << ((code + 1) >> 1)) >> 1; }
+
 struct DevTree {
     const int32_t *child;
     const int32_t *child_skip;
     const int32_t *top;        // [kTopCells] grid of `child`, or null
     const int32_t *top_skip;   // [kTopCells] grid of `child_skip`, or null
+    const uint32_t *brick_top;
+    const uint32_t *bricks;
     const void *rows;
     int32_t depth, sh_degree, K, storage;
     int32_t n_nodes, n_leaves, row_elems, pad;
@@ -100,6 +123,11 @@ hipError_t launch_query(const DevTree &t, const QueryArgs &a, bool trace, hipStr
 // trees/offsets are device arrays
 hipError_t launch_query_multi(int storage, int sh_degree, const DevTree *trees, const int64_t *offsets,
                               int n_trees, const QueryArgs &a, hipStream_t s);
+
+// Brick tables of the pruned child table (device memory) of a tree: one new
+// allocation *buf of *bytes that holds both tables.  Synchronous.
+hipError_t build_bricks(const int32_t *child_skip, int depth, uint32_t **buf, size_t *bytes, const uint32_t **brick_top,
+                        const uint32_t **bricks);
 
 // FP32 -> storage conversions used by the loader (round to nearest even)
 uint16_t f32_to_f16_rne(float x);

@@ -2,8 +2,9 @@
 // instantiated per storage type by octree_query_{f32,f16,bf16}.hip.
 //
 // Persistent waves: the grid holds as many 256-lane blocks as fit on the
-// chip at once.  Every lane marches one ray at a time (Marcher in march.h),
-// one octree node per step.  Every kStepsPerCheck steps the wave counts its
+// chip at once.  Every lane marches one ray at a time, one table entry per
+// step (BrickMarcher in march.h; the validation variants one octree node per
+// step, Marcher).  Every kStepsPerCheck steps the wave counts its
 // busy lanes; when fewer than kRefillBelow still hold a ray, the idle lanes
 // are refilled from a ray counter with one atomic per wave: a 64-bit ballot
 // of the idle lanes, one atomicAdd of its popcount by the lowest idle lane,
@@ -83,40 +84,74 @@ __device__ inline void write_ray(const QueryArgs &a, int64_t i, const M &m, bool
 
 __device__ inline int64_t range_begin(int x, int64_t n) { return n * x / kRanges; }
 
-// the persistent loop shared by the single- and multi-tree kernels;
-// tree_index(ray) finds the tree a ray queries (once, when a lane takes the
-// ray) and tree_at(k) returns tree k.  With TOP_LDS (one tree)
-// the block copies the tree's top grid into LDS; otherwise each ray reads
-// its tree's grid from global memory.  ORDER maps a position of the split
-// to a ray: kOrderAny takes a.index, then the image tile order, then the
-// position itself, whichever the arguments set; kOrderBatch only a.index or
-// the position; kOrderTiles only the tile order.
+// ORDER maps a position of the split to a ray: kOrderAny takes a.index, then
+// the image tile order, then the position itself, whichever the arguments
+// set; kOrderBatch only a.index or the position; kOrderTiles only the tile
+// order.
 enum { kOrderAny = 0, kOrderBatch = 1, kOrderTiles = 2 };
 
-template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP, bool TOP_LDS, int MODEL, int ORDER, class TreeIndex,
-          class TreeAt>
-__device__ inline void persistent_query(const QueryArgs &a, unsigned long long *queue, TreeIndex tree_index,
-                                        TreeAt tree_at) {
-    __shared__ int32_t s_path[10 * kBlock];   // per-lane node path, [level][lane]
-    int32_t *path = s_path + threadIdx.x;
-    const int32_t *top_lds = nullptr;
-    if constexpr (TOP_LDS) {
+// How a lane walks its ray.  OctreeWalk: node by node through the octree
+// (the validation variants).  The block copies the tree's top grid into LDS,
+// and each lane keeps its node path there.
+template <int ST, int DEG, bool ACC64, bool TRACE_, bool SKIP, int MODEL>
+struct OctreeWalk {
+    using M = Marcher<ST, DEG, ACC64, TRACE_, SKIP, MODEL>;
+    static constexpr bool TRACE = TRACE_;
+    int32_t *path;
+    const int32_t *top;
+    __device__ void setup(const DevTree &t0) {
+        __shared__ int32_t s_path[10 * kBlock];   // per-lane node path, [level][lane]
         __shared__ int32_t s_top[kTopCells];
-        const DevTree &t0 = tree_at(0);
+        path = s_path + threadIdx.x;
         const int32_t *src = SKIP ? t0.top_skip : t0.top;
-        if (src) {
+        top = src ? s_top : nullptr;
+        if (src)
             for (int i = threadIdx.x; i < kTopCells; i += kBlock) s_top[i] = src[i];
-            top_lds = s_top;
-        }
         __syncthreads();
     }
-    auto top_of = [&](const DevTree &t) -> const int32_t * {
-        if constexpr (TOP_LDS) return top_lds;
-        return SKIP ? t.top_skip : t.top;
-    };
+    __device__ bool step(M &m, const DevTree &t, const QueryArgs &a, uint32_t *ids) {
+        return m.step(t, a.model, a.flags, ids, TRACE ? a.max_ids : 0, path, kBlock, top);
+    }
+};
+
+// The same over several trees: each ray reads its tree's grid from global
+// memory.
+template <int ST, int DEG, bool ACC64, bool SKIP>
+struct MultiOctreeWalk {
+    using M = Marcher<ST, DEG, ACC64, false, SKIP, -1>;
+    static constexpr bool TRACE = false;
+    int32_t *path;
+    __device__ void setup(const DevTree &) {
+        __shared__ int32_t s_path[10 * kBlock];
+        path = s_path + threadIdx.x;
+    }
+    __device__ bool step(M &m, const DevTree &t, const QueryArgs &a, uint32_t *) {
+        return m.step(t, a.model, a.flags, nullptr, 0, path, kBlock, SKIP ? t.top_skip : t.top);
+    }
+};
+
+// BrickWalk: cell by cell through the brick tables (the plain queries).
+template <int ST, int DEG, int MODEL>
+struct BrickWalk {
+    using M = BrickMarcher<ST, DEG, MODEL>;
+    static constexpr bool TRACE = false;
+    __device__ void setup(const DevTree &) {}
+    __device__ bool step(M &m, const DevTree &t, const QueryArgs &a, uint32_t *) { return m.step(t, a.flags); }
+};
+
+// the persistent loop shared by all query kernels; tree_index(ray) finds the
+// tree a ray queries (once, when a lane takes the ray) and tree_at(k) returns
+// tree k.  Without counters (queue null) the launch has a lane for every ray
+// and each lane takes the ray at its own position.
+template <class Walk, int ORDER, class TreeIndex, class TreeAt>
+__device__ inline void persistent_query(const QueryArgs &a, unsigned long long *queue, TreeIndex tree_index,
+                                        TreeAt tree_at) {
+    constexpr bool TRACE = Walk::TRACE;
+    Walk walk;
+    walk.setup(tree_at(0));
     constexpr int refill_below = ORDER == kOrderTiles ? kTileRefillBelow : kRefillBelow;
     constexpr int steps_per_check = ORDER == kOrderTiles ? kTileStepsPerCheck : kStepsPerCheck;
-    Marcher<ST, DEG, ACC64, TRACE, SKIP, MODEL> m;
+    typename Walk::M m;
     int64_t ray = -1;            // ray held by this lane, -1 when idle
     int tk = 0;                  // tree of that ray
     uint32_t *ids = nullptr;
@@ -130,41 +165,46 @@ __device__ inline void persistent_query(const QueryArgs &a, unsigned long long *
         const int busy = __popcll(__ballot(ray >= 0));
         if (__builtin_expect(need && busy < refill_below, 0)) {
             for (int tries = 0; need && tries < kMaxTries; ++tries) {
-                const int cnt = __popcll(need);
-                const int leader = __ffsll((unsigned long long)need) - 1;
-                unsigned long long base = 0;
-                if ((int)__lane_id() == leader) base = atomicAdd(queue + cur, (unsigned long long)cnt);
-                const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)base, leader);
-                const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(base >> 32), leader);
-                base = ((unsigned long long)hi << 32) | lo;
-                const int64_t start = range_begin(cur, n);
-                const int64_t len = range_begin(cur + 1, n) - start;
-                if (want) {
+                int64_t pos = -1;    // position this lane takes up, if any
+                if (queue) {
+                    const int cnt = __popcll(need);
+                    const int leader = __ffsll((unsigned long long)need) - 1;
+                    unsigned long long base = 0;
+                    if ((int)__lane_id() == leader) base = atomicAdd(queue + cur, (unsigned long long)cnt);
+                    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)base, leader);
+                    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(base >> 32), leader);
+                    base = ((unsigned long long)hi << 32) | lo;
+                    const int64_t start = range_begin(cur, n);
+                    const int64_t len = range_begin(cur + 1, n) - start;
                     const int64_t slot = (int64_t)base + __popcll(need & lanemask_lt());
-                    if (slot < len) {
-                        const int64_t pos = start + slot;
-                        int64_t idx = pos;
-                        if constexpr (ORDER == kOrderTiles) {
-                            idx = tile_order_pixel((uint32_t)pos, a.img_w, a.img_h);
-                        } else {
-                            if (a.index) idx = a.index[pos];
-                            else if (ORDER == kOrderAny && a.img_w) idx = tile_order_pixel((uint32_t)pos, a.img_w, a.img_h);
-                        }
-                        ids = TRACE && a.max_ids > 0 ? a.leaf_ids + (size_t)idx * a.max_ids : nullptr;
-                        tk = tree_index(idx);
-                        if (m.init(tree_at(tk), a.o + 3 * idx, a.d + 3 * idx)) {
-                            ray = idx;
-                            want = false;
-                        } else {
-                            write_ray(a, idx, m, TRACE);   // no positive-length overlap: done
+                    if (want && slot < len) pos = start + slot;
+                    if ((int64_t)base + cnt >= len) {   // this range is used up: move on
+                        used_up |= 1ull << cur;
+                        for (int j = 1; j <= kRanges; ++j) {
+                            const int c = (cur + j) % kRanges;
+                            if (!(used_up & (1ull << c))) { cur = c; break; }
                         }
                     }
+                } else {
+                    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                    if (p < n) pos = p;
+                    used_up = kAllRanges;
                 }
-                if ((int64_t)base + cnt >= len) {   // this range is used up: move on
-                    used_up |= 1ull << cur;
-                    for (int j = 1; j <= kRanges; ++j) {
-                        const int c = (cur + j) % kRanges;
-                        if (!(used_up & (1ull << c))) { cur = c; break; }
+                if (pos >= 0) {
+                    int64_t idx = pos;
+                    if constexpr (ORDER == kOrderTiles) {
+                        idx = tile_order_pixel((uint32_t)pos, a.img_w, a.img_h);
+                    } else {
+                        if (a.index) idx = a.index[pos];
+                        else if (ORDER == kOrderAny && a.img_w) idx = tile_order_pixel((uint32_t)pos, a.img_w, a.img_h);
+                    }
+                    ids = TRACE && a.max_ids > 0 ? a.leaf_ids + (size_t)idx * a.max_ids : nullptr;
+                    tk = tree_index(idx);
+                    if (m.init(tree_at(tk), a.o + 3 * idx, a.d + 3 * idx)) {
+                        ray = idx;
+                        want = false;
+                    } else {
+                        write_ray(a, idx, m, TRACE);   // no positive-length overlap: done
                     }
                 }
                 want = want && used_up != kAllRanges;
@@ -173,8 +213,7 @@ __device__ inline void persistent_query(const QueryArgs &a, unsigned long long *
         }
         if (__all(ray < 0 && used_up == kAllRanges)) break;
         for (int k = 0; k < steps_per_check && ray >= 0; ++k) {
-            const DevTree &tr = tree_at(tk);
-            if (__builtin_expect(m.step(tr, a.model, a.flags, ids, TRACE ? a.max_ids : 0, path, kBlock, top_of(tr)), 0)) {
+            if (__builtin_expect(walk.step(m, tree_at(tk), a, ids), 0)) {
                 write_ray(a, ray, m, TRACE);
                 ray = -1;
             }
@@ -182,25 +221,21 @@ __device__ inline void persistent_query(const QueryArgs &a, unsigned long long *
     }
 }
 
-// MODEL >= 0 fixes the transmittance model at compile time (the plain
-// queries), -1 takes it from the arguments.
-template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP, int MODEL>
+// The validation kernels: traces, FP64 accumulation, every leaf composited;
+// the transmittance model and the ray order come from the arguments.
+template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP>
 __global__ __launch_bounds__(kBlock) void k_query(const DevTree t, const QueryArgs a,
                                                   unsigned long long *queue) {
-    persistent_query<ST, DEG, ACC64, TRACE, SKIP, true, MODEL, kOrderAny>(
+    persistent_query<OctreeWalk<ST, DEG, ACC64, TRACE, SKIP, -1>, kOrderAny>(
         a, queue, [](int64_t) { return 0; }, [&](int) -> const DevTree & { return t; });
 }
 
-// The plain query (float32 accumulation, no trace) with a register budget
-// for five waves per SIMD: it waits on dependent loads, and a fifth wave
+// The plain queries (float32 accumulation, no trace) with a register budget
+// for five waves per SIMD: they wait on dependent loads, and a fifth wave
 // hides more of that than the few values the budget moves out of registers
-// (spilled only on the path of rays that miss the box) cost.  Larger leaf
-// rows (SH degree 3 and 4) hold more values per lane -- the row and the
-// (l+1)^2 basis values -- and get a budget for fewer waves instead of
-// spilling them.  The validation variants keep the default budget, which
-// they need.  The kernels for one transmittance model take rays in batch
-// order or, with TILES, in the tile order of a camera batch; the
-// model-generic one (the validation flags) in whichever the arguments give.
+// cost.  Larger leaf rows (SH degree 3 and 4) hold more values per lane --
+// the row and the (l+1)^2 basis values -- and get a budget for fewer waves
+// instead of spilling them.
 template <int ST, int DEG>
 constexpr int plain_waves_per_simd() {
     constexpr int K = (DEG + 1) * (DEG + 1);
@@ -208,30 +243,29 @@ constexpr int plain_waves_per_simd() {
     return row_regs + K <= 40 ? 5 : (row_regs + K <= 70 ? 4 : 3);
 }
 
-template <int ST, int DEG, bool SKIP, int MODEL, bool TILES>
+// without the sigma_min skip (LQ_NO_SIGMA_SKIP): the full table
+template <int ST, int DEG>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd<ST, DEG>())))
-void k_query_plain(
-    const DevTree t, const QueryArgs a, unsigned long long *queue) {
-    constexpr int order = TILES ? kOrderTiles : (MODEL < 0 ? kOrderAny : kOrderBatch);
-    persistent_query<ST, DEG, false, false, SKIP, true, MODEL, order>(
+void k_query_full(const DevTree t, const QueryArgs a, unsigned long long *queue) {
+    persistent_query<OctreeWalk<ST, DEG, false, false, false, -1>, kOrderAny>(
         a, queue, [](int64_t) { return 0; }, [&](int) -> const DevTree & { return t; });
 }
 
-template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP, int MODEL, bool TILES>
-constexpr auto query_kernel() {
-    if constexpr (!ACC64 && !TRACE) return k_query_plain<ST, DEG, SKIP, MODEL, TILES>;
-    else return k_query<ST, DEG, ACC64, TRACE, SKIP, MODEL>;
+// the production query, in batch order or, with TILES, in the tile order of
+// a camera batch
+template <int ST, int DEG, int MODEL, bool TILES>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd<ST, DEG>())))
+void k_query_plain(const DevTree t, const QueryArgs a, unsigned long long *queue) {
+    persistent_query<BrickWalk<ST, DEG, MODEL>, TILES ? kOrderTiles : kOrderBatch>(
+        a, queue, [](int64_t) { return 0; }, [&](int) -> const DevTree & { return t; });
 }
 
 // several trees: rays [offsets[k], offsets[k+1]) query trees[k]; the tree of
-// a ray is found by binary search when a lane takes it.  The float32 kernels
-// are specialised on the model like the plain ones, but keep the default
-// register budget: a lane's tree fields come from memory and need registers
-// (with the five-wave budget they spill, 10.7 vs 7.9 ms on the uneven batch).
-template <int ST, int DEG, bool ACC64, bool SKIP, int MODEL>
-__device__ inline void multi_query(const DevTree *trees, const int64_t *offsets, int n_trees, const QueryArgs &a,
-                                   unsigned long long *queue) {
-    auto tree_index = [&](int64_t ray) {
+// a ray is found by binary search when a lane takes it.
+struct TreeOfRay {
+    const int64_t *offsets;
+    int n_trees;
+    __device__ int operator()(int64_t ray) const {
         int lo = 0, hi = n_trees;            // offsets[lo] <= ray < offsets[hi]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -239,22 +273,24 @@ __device__ inline void multi_query(const DevTree *trees, const int64_t *offsets,
             else hi = mid;
         }
         return lo;
-    };
-    persistent_query<ST, DEG, ACC64, false, SKIP, false, MODEL, kOrderBatch>(
-        a, queue, tree_index, [&](int k) -> const DevTree & { return trees[k]; });
-}
+    }
+};
 
 template <int ST, int DEG, bool ACC64, bool SKIP>
 __global__ __launch_bounds__(kBlock) void k_query_multi(const DevTree *trees, const int64_t *offsets,
                                                         int n_trees, const QueryArgs a,
                                                         unsigned long long *queue) {
-    multi_query<ST, DEG, ACC64, SKIP, -1>(trees, offsets, n_trees, a, queue);
+    persistent_query<MultiOctreeWalk<ST, DEG, ACC64, SKIP>, kOrderBatch>(
+        a, queue, TreeOfRay{offsets, n_trees}, [&](int k) -> const DevTree & { return trees[k]; });
 }
 
-template <int ST, int DEG, bool SKIP, int MODEL>
+// the plain multi-tree kernels keep the default register budget: a lane's
+// tree fields come from memory and need registers
+template <int ST, int DEG, int MODEL>
 __global__ __launch_bounds__(kBlock) void k_query_multi_plain(
     const DevTree *trees, const int64_t *offsets, int n_trees, const QueryArgs a, unsigned long long *queue) {
-    multi_query<ST, DEG, false, SKIP, MODEL>(trees, offsets, n_trees, a, queue);
+    persistent_query<BrickWalk<ST, DEG, MODEL>, kOrderBatch>(
+        a, queue, TreeOfRay{offsets, n_trees}, [&](int k) -> const DevTree & { return trees[k]; });
 }
 
 __global__ void k_zero_u64(unsigned long long *p) { p[threadIdx.x] = 0ull; }
@@ -280,21 +316,43 @@ int resident_blocks(Kern kern) {
     return nb;
 }
 
-template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP, int MODEL = -1, bool TILES = false>
-hipError_t launch_one(const DevTree &t, const QueryArgs &a, hipStream_t s) {
-    auto kern = query_kernel<ST, DEG, ACC64, TRACE, SKIP, MODEL, TILES>();
+// Launch over persistent blocks with ray counters.  kStatic: no counters when
+// the batch fits the chip at once and its size is known on the host; each
+// lane then takes one ray, without the counters' allocation, their clearing
+// launch and the refill atomics (4,096 rays on a depth-6 tree: 84 -> 35 us
+// with the brick march).  Batches of up to 64 K rays go out in one-wave
+// blocks, which spread over more CUs.
+template <bool kStatic, class Kern, class... Args>
+hipError_t launch_persistent(Kern kern, const QueryArgs &a, unsigned long long *queue, hipStream_t s, Args... args) {
     const int64_t need_blocks = (a.n + kBlock - 1) / kBlock;
     const int64_t nb = std::min<int64_t>(need_blocks, resident_blocks(kern));
-    unsigned long long *queue = a.counters;
+    if (kStatic && nb == need_blocks && !a.n_dev) {
+        const int block = a.n <= (int64_t)64 * 1024 ? 64 : kBlock;
+        hipLaunchKernelGGL(kern, dim3((unsigned)((a.n + block - 1) / block)), dim3(block), 0, s, args...,
+                           (unsigned long long *)nullptr);
+        return hipGetLastError();
+    }
     hipError_t e = hipSuccess;
-    if (!queue && (e = hipMallocAsync((void **)&queue, kRanges * sizeof(unsigned long long), s)) != hipSuccess)
-        return e;
+    const bool own = !queue;
+    if (own && (e = hipMallocAsync((void **)&queue, kRanges * sizeof(unsigned long long), s)) != hipSuccess) return e;
     // cleared by a kernel (not a memset node), so the launch can be captured
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(kRanges), 0, s, queue);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kBlock), 0, s, t, a, queue);
+    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kBlock), 0, s, args..., queue);
     e = hipGetLastError();
-    hipError_t f = a.counters ? hipSuccess : hipFreeAsync(queue, s);
+    const hipError_t f = own ? hipFreeAsync(queue, s) : hipSuccess;
     return e != hipSuccess ? e : f;
+}
+
+template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP>
+hipError_t launch_checked(const DevTree &t, const QueryArgs &a, hipStream_t s) {
+    return launch_persistent<false>(k_query<ST, DEG, ACC64, TRACE, SKIP>, a, a.counters, s, t, a);
+}
+
+template <int ST, int DEG, int MODEL>
+hipError_t launch_plain(const DevTree &t, const QueryArgs &a, hipStream_t s) {
+    // the kernels of camera batches have the tile order built in
+    return a.img_w ? launch_persistent<true>(k_query_plain<ST, DEG, MODEL, true>, a, a.counters, s, t, a)
+                   : launch_persistent<true>(k_query_plain<ST, DEG, MODEL, false>, a, a.counters, s, t, a);
 }
 
 template <int ST, int DEG>
@@ -304,18 +362,13 @@ hipError_t launch_deg(const DevTree &t, const QueryArgs &a, bool trace, hipStrea
     const bool acc64 = (a.flags & LQ_FP64_ACCUM) != 0;
     const bool full = trace || (a.flags & LQ_NO_SIGMA_SKIP) != 0;
     // a trace of the pruned table (the production query's work)
-    if (trace && (a.flags & LQ_TRACE_PRUNED)) return launch_one<ST, DEG, false, true, true>(t, a, s);
-    if (trace) return acc64 ? launch_one<ST, DEG, true, true, false>(t, a, s)
-                            : launch_one<ST, DEG, false, true, false>(t, a, s);
-    if (full) return acc64 ? launch_one<ST, DEG, true, false, false>(t, a, s)
-                           : launch_one<ST, DEG, false, false, false>(t, a, s);
-    if (acc64) return launch_one<ST, DEG, true, false, true>(t, a, s);
-    // the plain kernels of camera batches have the tile order built in
-    if (a.img_w)
-        return a.model == LQ_EXP ? launch_one<ST, DEG, false, false, true, LQ_EXP, true>(t, a, s)
-                                 : launch_one<ST, DEG, false, false, true, LQ_LINEAR, true>(t, a, s);
-    return a.model == LQ_EXP ? launch_one<ST, DEG, false, false, true, LQ_EXP>(t, a, s)
-                             : launch_one<ST, DEG, false, false, true, LQ_LINEAR>(t, a, s);
+    if (trace && (a.flags & LQ_TRACE_PRUNED)) return launch_checked<ST, DEG, false, true, true>(t, a, s);
+    if (trace) return acc64 ? launch_checked<ST, DEG, true, true, false>(t, a, s)
+                            : launch_checked<ST, DEG, false, true, false>(t, a, s);
+    if (full) return acc64 ? launch_checked<ST, DEG, true, false, false>(t, a, s)
+                           : launch_persistent<false>(k_query_full<ST, DEG>, a, a.counters, s, t, a);
+    if (acc64) return launch_checked<ST, DEG, true, false, true>(t, a, s);
+    return a.model == LQ_EXP ? launch_plain<ST, DEG, LQ_EXP>(t, a, s) : launch_plain<ST, DEG, LQ_LINEAR>(t, a, s);
 }
 
 template <int ST>
@@ -330,35 +383,20 @@ hipError_t launch_st(const DevTree &t, const QueryArgs &a, bool trace, hipStream
     return hipErrorInvalidValue;
 }
 
-template <int ST, int DEG, bool ACC64, bool SKIP, int MODEL = -1>
-hipError_t launch_multi_one(const DevTree *trees, const int64_t *offsets, int n_trees, const QueryArgs &a,
-                            hipStream_t s) {
-    auto kern = [] {
-        if constexpr (!ACC64 && MODEL >= 0) return k_query_multi_plain<ST, DEG, SKIP, MODEL>;
-        else return k_query_multi<ST, DEG, ACC64, SKIP>;
-    }();
-    const int64_t need_blocks = (a.n + kBlock - 1) / kBlock;
-    const int64_t nb = std::min<int64_t>(need_blocks, resident_blocks(kern));
-    unsigned long long *queue = nullptr;
-    hipError_t e = hipMallocAsync((void **)&queue, kRanges * sizeof(unsigned long long), s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(kRanges), 0, s, queue);
-    hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kBlock), 0, s, trees, offsets, n_trees, a, queue);
-    e = hipGetLastError();
-    hipError_t f = hipFreeAsync(queue, s);
-    return e != hipSuccess ? e : f;
-}
-
 template <int ST, int DEG>
 hipError_t launch_multi_deg(const DevTree *trees, const int64_t *offsets, int n_trees, const QueryArgs &a,
                             hipStream_t s) {
     const bool acc64 = (a.flags & LQ_FP64_ACCUM) != 0;
     const bool full = (a.flags & LQ_NO_SIGMA_SKIP) != 0;
-    if (full) return acc64 ? launch_multi_one<ST, DEG, true, false>(trees, offsets, n_trees, a, s)
-                           : launch_multi_one<ST, DEG, false, false>(trees, offsets, n_trees, a, s);
-    if (acc64) return launch_multi_one<ST, DEG, true, true>(trees, offsets, n_trees, a, s);
-    return a.model == LQ_EXP ? launch_multi_one<ST, DEG, false, true, LQ_EXP>(trees, offsets, n_trees, a, s)
-                             : launch_multi_one<ST, DEG, false, true, LQ_LINEAR>(trees, offsets, n_trees, a, s);
+    const auto checked = [&](auto kern) {
+        return launch_persistent<false>(kern, a, nullptr, s, trees, offsets, n_trees, a);
+    };
+    const auto plain = [&](auto kern) {
+        return launch_persistent<true>(kern, a, nullptr, s, trees, offsets, n_trees, a);
+    };
+    if (full) return acc64 ? checked(k_query_multi<ST, DEG, true, false>) : checked(k_query_multi<ST, DEG, false, false>);
+    if (acc64) return checked(k_query_multi<ST, DEG, true, true>);
+    return a.model == LQ_EXP ? plain(k_query_multi_plain<ST, DEG, LQ_EXP>) : plain(k_query_multi_plain<ST, DEG, LQ_LINEAR>);
 }
 
 template <int ST>
