@@ -780,6 +780,25 @@ LQ_HD inline float fract(float x) {
 #endif
 }
 
+// NW words of a 16-byte aligned row, and no more: a register that a load in
+// flight will write, though nothing reads it, could not be used meanwhile
+template <int NW>
+LQ_HD inline void load_row(const char *row, uint32_t (&w)[NW]) {
+    constexpr int whole = NW / 4, rest = NW % 4;
+    const uint4 *p = reinterpret_cast<const uint4 *>(row);
+#pragma unroll
+    for (int c = 0; c < whole; ++c) {
+        const uint4 v = p[c];
+        w[4 * c] = v.x; w[4 * c + 1] = v.y; w[4 * c + 2] = v.z; w[4 * c + 3] = v.w;
+    }
+    const uint32_t *q = reinterpret_cast<const uint32_t *>(row) + 4 * whole;
+    if constexpr (rest >= 2) {
+        const uint2 v = *reinterpret_cast<const uint2 *>(q);
+        w[4 * whole] = v.x; w[4 * whole + 1] = v.y;
+    }
+    if constexpr (rest % 2 == 1) w[NW - 1] = q[rest - 1];
+}
+
 // true when the filter certifies the parameter of approximation tb >= 0 to be
 // later than that of ta: both are within 3.0000002 u of their own value (u =
 // 2^-24), so tb (1 - 8 u) > ta leaves 8 u tb > 6.0000004 u tb after the
@@ -813,7 +832,7 @@ struct BrickMarcher {
     static constexpr int K = (DEG + 1) * (DEG + 1);
     static constexpr int RB = row_bytes_for(S::bytes, K);
     static constexpr int NE = 1 + 3 * K;
-    static constexpr int NCH = (NE * S::bytes + 15) / 16;   // 16-byte chunks holding the row
+    static constexpr int NW = (NE * S::bytes + 3) / 4;      // words holding the row
 
     Ray r;                // mirrored; inv is +inf where d is 0
     float dlen;
@@ -825,16 +844,26 @@ struct BrickMarcher {
     float ev_P, ev_o, ev_d, ev_inv;   // its plane, and the ray along its axis
     uint32_t flip;        // bit a: axis a is mirrored
     uint32_t top_entry;   // brick_top entry of the brick that holds q
+    uint32_t entry;       // entry of q: the brick's, or that of its cell
 
-    // Entry of the brick that holds q.  x, y, z of the table are q with the
-    // bits of the mirrored axes inverted.
-    LQ_HD void load_top(const DevTree &t) {
-        const int b = brick_top_bits(t.depth);
-        const uint32_t m = (1u << b) - 1u;
-        const uint32_t inv_bits = ((flip & 1u) ? m : 0u) | ((flip & 2u) ? m << b : 0u) | ((flip & 4u) ? m << (2 * b) : 0u);
-        const uint32_t i = (((uint32_t)q[2] >> kBrickBits) << (2 * b)) | (((uint32_t)q[1] >> kBrickBits) << b) |
-                           ((uint32_t)q[0] >> kBrickBits);
-        top_entry = t.brick_top[i ^ inv_bits];
+    // The entries of q, the grid's only when the ray came into a new brick.
+    // x, y, z of the tables are q with the bits of the mirrored axes inverted.
+    LQ_HD void load_cell(const DevTree &t, bool new_brick) {
+        const auto inverted = [&](uint32_t m, int b) {
+            return ((flip & 1u) ? m : 0u) | ((flip & 2u) ? m << b : 0u) | ((flip & 4u) ? m << (2 * b) : 0u);
+        };
+        if (new_brick) {
+            const int b = brick_top_bits(t.depth);
+            const uint32_t i = (((uint32_t)q[2] >> kBrickBits) << (2 * b)) | (((uint32_t)q[1] >> kBrickBits) << b) |
+                               ((uint32_t)q[0] >> kBrickBits);
+            top_entry = t.brick_top[i ^ inverted((1u << b) - 1u, b)];
+        }
+        entry = top_entry;
+        if (top_entry & kBrickFull) {
+            const uint32_t i = (((uint32_t)q[2] & 7u) << 6) | (((uint32_t)q[1] & 7u) << 3) | ((uint32_t)q[0] & 7u);
+            const uint32_t m = t.depth < kBrickBits ? (1u << t.depth) - 1u : 7u;
+            entry = t.bricks[(top_entry << 9) + (i ^ inverted(m, kBrickBits))];   // the full bit leaves with the shift
+        }
     }
 
     LQ_HD void mirror(int N) {
@@ -885,13 +914,13 @@ struct BrickMarcher {
         const float inv_len = 1.0f / dlen;
         sh_basis<DEG>(-r.d[0] * inv_len, -r.d[1] * inv_len, -r.d[2] * inv_len, Y);
         // Margin of a cell coordinate g = (p + 1) N / 2, p = o + t d: t is
-        // within 3.0000002 u of its own value, the two fmas round once each,
-        // and on an axis that the ray has not left |p| is at most the
-        // farthest plane a box can reach, B = 1 + 2 (16 << kBrickBits) / N, so
-        // |t d| <= B + |o|; 8 u covers the sum with margin.
-        const float B = 1.0f + (float)(32 << kBrickBits) / (float)N;
+        // within 3.0000002 u of its own value (u = 2^-24) and the two fmas
+        // round once each, so g is off by under
+        //     (3.0000002 |t d| + 2 |p| + 1) u N / 2,   |t d| <= |p| + |o|,
+        // which for |p| <= 1.1 is under the margin taken here; a coordinate
+        // beyond that is past the grid whichever way it rounds.
         const float omax = fmaxf(fmaxf(fabsf(r.o[0]), fabsf(r.o[1])), fabsf(r.o[2]));
-        thr = 0.5f - (2.0f * B + omax + 2.0f) * (half_n * 0x1p-21f);
+        thr = 0.5f - (3.25f * omax + 7.0f) * (half_n * 0x1p-24f);
 
         // ---- fast path: a ray from outside the box whose entry is certified
         if (__builtin_expect(plain, 1)) {
@@ -931,7 +960,7 @@ struct BrickMarcher {
                         q[ax] = k[ax];
                     }
                     set_event(ea, -1.0f);
-                    load_top(t);
+                    load_cell(t, true);
                     return true;
                 }
             }
@@ -1010,7 +1039,7 @@ struct BrickMarcher {
         for (int ax = 0; ax < 3; ++ax)
             if (r.d[ax] == 0.0f) r.inv[ax] = INFINITY;
         set_event(ev.ax, -1.0f);
-        load_top(t);
+        load_cell(t, true);
         return true;
     }
 
@@ -1020,17 +1049,13 @@ struct BrickMarcher {
         const int N = 1 << t.depth;
         const float h = 2.0f / (float)N, half_n = 0.5f * (float)N;
         // ---- what the cell holds: a leaf, or how far the empty space reaches
-        uint32_t e = top_entry;
-        int low = 7, unit = kBrickBits;       // an empty brick: whole bricks from its lower corner
-        if (e & kBrickFull) {
-            uint32_t i = (((uint32_t)q[2] & 7u) << 6) | (((uint32_t)q[1] & 7u) << 3) | ((uint32_t)q[0] & 7u);
-            const uint32_t m = t.depth < kBrickBits ? (1u << t.depth) - 1u : 7u;
-            i ^= ((flip & 1u) ? m : 0u) | ((flip & 2u) ? m << 3 : 0u) | ((flip & 4u) ? m << 6 : 0u);
-            e = t.bricks[(e << 9) + i];       // the full bit leaves with the shift
-            low = 0;
-            unit = 0;
-        }
+        const uint32_t e = entry;
         const bool is_leaf = (e & kBrickFull) != 0;
+        uint32_t w[NW];
+        if (is_leaf) load_row<NW>(static_cast<const char *>(t.rows) + (size_t)(e & ~kBrickFull) * RB, w);
+        // an empty brick: whole bricks from its lower corner
+        const bool coarse = !(top_entry & kBrickFull);
+        const int low = coarse ? 7 : 0, unit = coarse ? kBrickBits : 0;
         const int code = (int)((e >> (3u * flip)) & 7u);
         const int reach = is_leaf ? 0 : (brick_extent(code) - 1) << unit;
         int last[3];                          // the box's last cell along each axis
@@ -1053,24 +1078,21 @@ struct BrickMarcher {
             const float g = fmaf(fmaf(xt, r.d[ax], r.o[ax]), half_n, half_n);
             const bool out = ax == xa;
             // within a leaf the other axes stay in their cell
-            fast = fast && (out || is_leaf || fabsf(fract(g) - 0.5f) < thr);
+            fast &= out | is_leaf | (fabsf(fract(g) - 0.5f) < thr);
             const int k = out ? last[ax] + 1 : (int)g;
             nq[ax] = is_leaf && !out ? q[ax] : k;
         }
-        fast = fast && thr >= 0.0f;
+        fast &= thr >= 0.0f;
         if (__builtin_expect(!fast, 0)) exact_exit(t, last, xa, xP, nq);
-        const float xo = xa == 0 ? r.o[0] : (xa == 1 ? r.o[1] : r.o[2]);
-        const float xd = xa == 0 ? r.d[0] : (xa == 1 ? r.d[1] : r.d[2]);
-        const float xi = xa == 0 ? r.inv[0] : (xa == 1 ? r.inv[1] : r.inv[2]);
+        const float xo = sel3v(r.o, xa), xd = sel3v(r.d, xa), xi = sel3v(r.inv, xa);
+        // ---- the next cell's entries, on their way while the leaf is composited
+        const bool leaving = (nq[0] >= N) | (nq[1] >= N) | (nq[2] >= N);
+        if (!leaving) {
+            const int moved = (q[0] ^ nq[0]) | (q[1] ^ nq[1]) | (q[2] ^ nq[2]);
+            q[0] = nq[0]; q[1] = nq[1]; q[2] = nq[2];
+            load_cell(t, (moved >> kBrickBits) != 0);
+        }
         if (is_leaf) {
-            const uint4 *rowp = reinterpret_cast<const uint4 *>(static_cast<const char *>(t.rows) +
-                                                                (size_t)(e & ~kBrickFull) * RB);
-            uint32_t w[NCH * 4];
-#pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) {
-                const uint4 cc = rowp[ch];
-                w[4 * ch] = cc.x; w[4 * ch + 1] = cc.y; w[4 * ch + 2] = cc.z; w[4 * ch + 3] = cc.w;
-            }
             // segment length, as seg_dt (event at the origin, same axis, or
             // two axes)
             float X1, X0, V1, V0;
@@ -1104,11 +1126,8 @@ struct BrickMarcher {
             T -= wgt;
             if (!(flags & LQ_NO_EARLY_TERM) && (1.0f - T) >= t.alpha_max) return true;
         }
-        if (__builtin_expect(nq[0] >= N || nq[1] >= N || nq[2] >= N, 0)) return true;
-        const int moved = (q[0] ^ nq[0]) | (q[1] ^ nq[1]) | (q[2] ^ nq[2]);
-        q[0] = nq[0]; q[1] = nq[1]; q[2] = nq[2];
+        if (__builtin_expect(leaving, 0)) return true;
         ev_ax = xa; ev_P = xP; ev_o = xo; ev_d = xd; ev_inv = xi;
-        if (moved >> kBrickBits) load_top(t);
         return false;
     }
 
