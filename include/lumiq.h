@@ -130,8 +130,8 @@ lq_status lq_query_radiance(const lq_octree *tree, const float *origins, const f
  * lq_query_radiance without any device allocation, for callers that cannot
  * allocate: code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, results (bit for bit), flags and
- * errors as lq_query_radiance.  The launch's only scratch -- 16 ray
- * counters, 128 bytes, whatever n -- lives in a static device array of the
+ * errors as lq_query_radiance.  The launch's only scratch -- 8 ray
+ * counters, 2 KB, whatever n -- lives in a static device array of the
  * library (one copy per GPU, held until the process ends), cleared by a
  * kernel at the start of every call.  Every call on one GPU shares that
  * array: calls that overlap in time on one GPU (concurrent streams, or

@@ -63,9 +63,10 @@ struct DevTree {
     float l_max, sigma_min, alpha_max, pad2;
 };
 
-// Ray counters of one query launch (two contiguous ranges of the batch per
-// accelerator die, see octree_kernels.h).
-constexpr int kQueryCounters = 16;
+// Words of the ray counters of one query launch: one per accelerator die, each
+// in a line of its own (see octree_kernels.h).
+constexpr int kCounterStride = 32;
+constexpr int kQueryCounters = 8 * kCounterStride;
 
 struct QueryArgs {
     const float *o, *d;
@@ -89,7 +90,7 @@ struct QueryArgs {
     // of a row-major image and the waves take them up in 8 x 8 pixel tiles
     // (tile_order_pixel); excludes index
     uint32_t img_w, img_h;
-    // kQueryCounters device counters for the launch, or null: the launcher
+    // kQueryCounters words for the launch's counters, or null: the launcher
     // then allocates them stream-ordered
     unsigned long long *counters;
 };

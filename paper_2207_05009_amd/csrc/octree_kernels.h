@@ -4,29 +4,36 @@
 // Persistent waves: the grid holds as many 256-lane blocks as fit on the
 // chip at once.  Every lane marches one ray at a time, one table entry per
 // step (BrickMarcher in march.h; the validation variants one octree node per
-// step, Marcher).  Every kStepsPerCheck steps the wave counts its
-// busy lanes; when fewer than kRefillBelow still hold a ray, the idle lanes
-// are refilled from a ray counter with one atomic per wave: a 64-bit ballot
-// of the idle lanes, one atomicAdd of its popcount by the lowest idle lane,
-// and each idle lane takes base + (number of idle lanes below it).  Rays of very different lengths
-// then do not leave most of a wave idle until its longest ray is done,
-// while the atomic's latency and the per-ray set-up are paid for many lanes
-// at once.
+// step, Marcher).  Every kStepsPerCheck steps the wave counts its busy lanes;
+// when fewer than kRefillBelow still hold a ray, the idle lanes are refilled:
+// each takes the wave's next position plus the number of idle lanes below it.
+// Rays of very different lengths then do not leave most of a wave idle until
+// its longest ray is done, while the per-ray set-up is paid for many lanes at
+// once.
 //
-// XCD-aware work split: the batch is cut into kXcds groups of kRangesPerXcd
-// contiguous ranges, with a counter each.  Workgroups are dispatched to the
-// accelerator dies round robin, so a wave of block b starts on a range of
-// group b % kXcds: the rays one die's L2 sees are neighbours in the batch
-// (for a camera, a band of image rows), not every kXcds-th chunk.  Two
-// counters per die rather than one halve the same-address atomics of the
-// refills, which bound batches of short or dead rays; more counters spread a
-// die's waves over too many places of the batch for its L2.  A wave whose
-// range is used up continues on the next ranges, so the tail stays balanced.
+// A wave reserves positions in chunks from a ray counter, one atomic each.
+// The counters lie kCounterStride words apart: with all of them in one
+// 128-byte line, and an atomic per refill, these atomics (about 10 ns each,
+// one after the other) were what bounded batches of short rays -- refilling
+// more often made the launch slower.  Counters of their own lines and chunks
+// of 128: 4.2M room rays, float16, 1.49 -> 1.02 ms, 3M rays over 12 trees
+// 0.82 -> 0.55 ms.
+//
+// XCD-aware work split: the batch is cut into kXcds contiguous ranges, with a
+// counter each.  Workgroups are dispatched to the accelerator dies round
+// robin, so a wave of block b starts on range b % kXcds: the rays one die's
+// L2 sees are neighbours in the batch (for a camera, a band of image rows),
+// not every kXcds-th chunk (two ranges per die: camera 0.93 -> 1.03 ms).  A
+// wave whose range is used up continues on the next ranges, so the tail stays
+// balanced.
 //
 // Camera batches are split by position in their tile order instead
-// (tile_order_pixel): the 64 rays one refill hands a wave then form an 8 x 8
-// pixel tile rather than a 1 x 64 strip of a row, so the lanes of a wave
-// descend through mostly the same nodes and read mostly the same leaf rows.
+// (tile_order_pixel), in chunks of one 8 x 8 pixel tile, and a wave takes the
+// next tile when it is done with the last: its lanes then march neighbouring
+// pixels, cell by cell through mostly the same bricks and leaf rows.  Mixing
+// the rest of one tile with rays of the next (refill below 16 busy lanes)
+// costs more in cache lines than the idle lanes do: 0.93 -> 0.77 ms, and the
+// exponential model with float16 rows alike.
 #include <mutex>
 #include <unordered_map>
 
@@ -41,18 +48,17 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kRefillBelow = 40;     // refill when fewer lanes of a wave are busy
-constexpr int kStepsPerCheck = 10;   // steps between refill checks
-// the same for camera batches in tile order, whose rays in a wave (one
-// pixel tile) end at similar steps: fewer checks pay more than early refills
-constexpr int kTileRefillBelow = 16;
-constexpr int kTileStepsPerCheck = 32;
+constexpr int kStepsPerCheck = 4;    // steps between refill checks
+constexpr int kTileStepsPerCheck = 16;
 constexpr int kXcds = 8;             // accelerator dies (XCDs) of an MI355X
-constexpr int kRangesPerXcd = 2;     // ray counters (contiguous ranges) per die
-constexpr int kRanges = kXcds * kRangesPerXcd;
-static_assert(kRanges == kQueryCounters, "one counter per range");
-static_assert(kRanges >= 1 && kRanges <= 64, "one bit per range in a 64-bit mask");
-constexpr uint64_t kAllRanges = kRanges == 64 ? ~0ull : (1ull << kRanges) - 1ull;   // every range used up
+constexpr int kRanges = kXcds;       // ray counters (contiguous ranges)
+static_assert(kRanges * kCounterStride == kQueryCounters, "the counters of a launch");
+constexpr uint32_t kAllRanges = (1u << kRanges) - 1u;   // every range used up
 constexpr int kMaxTries = 8;         // refill attempts per check
+// positions per reservation: a tile of a camera batch; otherwise kChunk, or
+// half of it when the batch would leave a wave fewer than two such chunks
+constexpr int kTile = 64;
+constexpr int kChunk = 128;
 
 __device__ inline uint64_t lanemask_lt() {
     const unsigned lane = __lane_id();
@@ -149,42 +155,46 @@ __device__ inline void persistent_query(const QueryArgs &a, unsigned long long *
     constexpr bool TRACE = Walk::TRACE;
     Walk walk;
     walk.setup(tree_at(0));
-    constexpr int refill_below = ORDER == kOrderTiles ? kTileRefillBelow : kRefillBelow;
-    constexpr int steps_per_check = ORDER == kOrderTiles ? kTileStepsPerCheck : kStepsPerCheck;
+    constexpr bool tiles = ORDER == kOrderTiles;
+    constexpr int refill_below = tiles ? 1 : kRefillBelow;
+    constexpr int steps_per_check = tiles ? kTileStepsPerCheck : kStepsPerCheck;
     typename Walk::M m;
     int64_t ray = -1;            // ray held by this lane, -1 when idle
     int tk = 0;                  // tree of that ray
     uint32_t *ids = nullptr;
-    // range this wave draws from (wave-uniform): one of its die's ranges
-    int cur = (int)(blockIdx.x % kXcds) * kRangesPerXcd + (int)((blockIdx.x / kXcds) % kRangesPerXcd);
-    uint64_t used_up = 0;           // ranges known to be exhausted (wave-uniform)
+    int cur = (int)(blockIdx.x % kXcds);   // range this wave reserves from (wave-uniform)
+    uint32_t used_up = 0;                  // ranges known to be exhausted (wave-uniform)
+    int64_t pool = 0, pool_end = 0;        // positions reserved for this wave (wave-uniform)
     const int64_t n = a.n_dev ? (int64_t)*a.n_dev : a.n;
+    const int chunk = tiles || n < (int64_t)gridDim.x * (kBlock / 64) * (2 * kChunk) ? kTile : kChunk;
     for (;;) {
-        bool want = ray < 0 && used_up != kAllRanges;
+        bool want = ray < 0 && (pool < pool_end || used_up != kAllRanges);
         uint64_t need = __ballot(want);
         const int busy = __popcll(__ballot(ray >= 0));
         if (__builtin_expect(need && busy < refill_below, 0)) {
             for (int tries = 0; need && tries < kMaxTries; ++tries) {
                 int64_t pos = -1;    // position this lane takes up, if any
                 if (queue) {
-                    const int cnt = __popcll(need);
-                    const int leader = __ffsll((unsigned long long)need) - 1;
-                    unsigned long long base = 0;
-                    if ((int)__lane_id() == leader) base = atomicAdd(queue + cur, (unsigned long long)cnt);
-                    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)base, leader);
-                    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(base >> 32), leader);
-                    base = ((unsigned long long)hi << 32) | lo;
-                    const int64_t start = range_begin(cur, n);
-                    const int64_t len = range_begin(cur + 1, n) - start;
-                    const int64_t slot = (int64_t)base + __popcll(need & lanemask_lt());
-                    if (want && slot < len) pos = start + slot;
-                    if ((int64_t)base + cnt >= len) {   // this range is used up: move on
-                        used_up |= 1ull << cur;
-                        for (int j = 1; j <= kRanges; ++j) {
-                            const int c = (cur + j) % kRanges;
-                            if (!(used_up & (1ull << c))) { cur = c; break; }
+                    if (pool == pool_end) {    // reserve the next chunk
+                        unsigned long long base = 0;
+                        if (__lane_id() == 0) base = atomicAdd(queue + cur * kCounterStride, (unsigned long long)chunk);
+                        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
+                        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+                        base = ((unsigned long long)hi << 32) | lo;
+                        const int64_t start = range_begin(cur, n), end = range_begin(cur + 1, n);
+                        pool = std::min<int64_t>(start + (int64_t)base, end);
+                        pool_end = std::min<int64_t>(pool + chunk, end);
+                        if (pool_end == end) {   // this range is used up: the next reservation is from another
+                            used_up |= 1u << cur;
+                            for (int j = 1; j <= kRanges; ++j) {
+                                const int c = (cur + j) % kRanges;
+                                if (!(used_up & (1u << c))) { cur = c; break; }
+                            }
                         }
                     }
+                    const int64_t p = pool + __popcll(need & lanemask_lt());
+                    if (want && p < pool_end) pos = p;
+                    pool = std::min<int64_t>(pool + __popcll(need), pool_end);
                 } else {
                     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
                     if (p < n) pos = p;
@@ -207,11 +217,11 @@ __device__ inline void persistent_query(const QueryArgs &a, unsigned long long *
                         write_ray(a, idx, m, TRACE);   // no positive-length overlap: done
                     }
                 }
-                want = want && used_up != kAllRanges;
+                want = want && (pool < pool_end || used_up != kAllRanges);
                 need = __ballot(want);
             }
         }
-        if (__all(ray < 0 && used_up == kAllRanges)) break;
+        if (__all(ray < 0) && pool == pool_end && used_up == kAllRanges) break;
         for (int k = 0; k < steps_per_check && ray >= 0; ++k) {
             if (__builtin_expect(walk.step(m, tree_at(tk), a, ids), 0)) {
                 write_ray(a, ray, m, TRACE);
@@ -230,22 +240,29 @@ __global__ __launch_bounds__(kBlock) void k_query(const DevTree t, const QueryAr
         a, queue, [](int64_t) { return 0; }, [&](int) -> const DevTree & { return t; });
 }
 
-// The plain queries (float32 accumulation, no trace) with a register budget
-// for five waves per SIMD: they wait on dependent loads, and a fifth wave
-// hides more of that than the few values the budget moves out of registers
-// cost.  Larger leaf rows (SH degree 3 and 4) hold more values per lane --
-// the row and the (l+1)^2 basis values -- and get a budget for fewer waves
-// instead of spilling them.
+// Register budgets of the plain queries (float32 accumulation, no trace), in
+// waves per SIMD: they wait on dependent loads, so as many waves as hold the
+// leaf row and the (l+1)^2 basis values in registers, up to 16 bytes per lane
+// of which the budget may move to scratch (float32, degree 2: camera 0.77 ms
+// with four waves, 0.71 with five).  Beyond that spilling costs more than the
+// wave gains (float16, degree 3: 0.28 ms with four waves, 0.61 with five).
 template <int ST, int DEG>
 constexpr int plain_waves_per_simd() {
+    constexpr int K = (DEG + 1) * (DEG + 1);
+    if (ST == LQ_F32) return K <= 9 ? 5 : 4;
+    return K <= 4 ? 5 : (K <= 16 ? 4 : 3);
+}
+
+// without the sigma_min skip (LQ_NO_SIGMA_SKIP): the full table
+template <int ST, int DEG>
+constexpr int full_waves_per_simd() {
     constexpr int K = (DEG + 1) * (DEG + 1);
     constexpr int row_regs = ((1 + 3 * K) * Storage<ST>::bytes + 15) / 16 * 4;
     return row_regs + K <= 40 ? 5 : (row_regs + K <= 70 ? 4 : 3);
 }
 
-// without the sigma_min skip (LQ_NO_SIGMA_SKIP): the full table
 template <int ST, int DEG>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd<ST, DEG>())))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(full_waves_per_simd<ST, DEG>())))
 void k_query_full(const DevTree t, const QueryArgs a, unsigned long long *queue) {
     persistent_query<OctreeWalk<ST, DEG, false, false, false, -1>, kOrderAny>(
         a, queue, [](int64_t) { return 0; }, [&](int) -> const DevTree & { return t; });
@@ -293,7 +310,7 @@ __global__ __launch_bounds__(kBlock) void k_query_multi_plain(
         a, queue, TreeOfRay{offsets, n_trees}, [&](int k) -> const DevTree & { return trees[k]; });
 }
 
-__global__ void k_zero_u64(unsigned long long *p) { p[threadIdx.x] = 0ull; }
+__global__ void k_zero_u64(unsigned long long *p) { p[threadIdx.x * kCounterStride] = 0ull; }
 
 // resident blocks of a kernel on the current device (cached)
 template <class Kern>
@@ -334,7 +351,7 @@ hipError_t launch_persistent(Kern kern, const QueryArgs &a, unsigned long long *
     }
     hipError_t e = hipSuccess;
     const bool own = !queue;
-    if (own && (e = hipMallocAsync((void **)&queue, kRanges * sizeof(unsigned long long), s)) != hipSuccess) return e;
+    if (own && (e = hipMallocAsync((void **)&queue, kQueryCounters * sizeof(unsigned long long), s)) != hipSuccess) return e;
     // cleared by a kernel (not a memset node), so the launch can be captured
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(kRanges), 0, s, queue);
     hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kBlock), 0, s, args..., queue);
