@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "lq_internal.h"
+#include "storage.h"
 
 struct lq_octree {
     int device;
@@ -37,43 +38,16 @@ static lq_status hip_fail(hipError_t e, const char *what) {
     return fail(LQ_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// ------------------------------------------------------------ conversions
-uint16_t f32_to_f16_rne(float x) {
-    uint32_t u;
-    memcpy(&u, &x, 4);
-    uint32_t sign = (u >> 16) & 0x8000u;
-    uint32_t ex = (u >> 23) & 0xFFu;
-    uint32_t man = u & 0x7FFFFFu;
-    if (ex == 0xFFu) return (uint16_t)(sign | 0x7C00u | (man ? 0x200u : 0u));
-    int e = (int)ex - 127 + 15;
-    if (e >= 31) return (uint16_t)(sign | 0x7C00u);          // overflow -> inf
-    if (e <= 0) {                                             // subnormal or zero
-        if (e < -10) return (uint16_t)sign;
-        man |= 0x800000u;
-        int shift = 14 - e;                                   // 1 - e + 13
-        uint32_t half = man >> shift;
-        uint32_t rem = man & ((1u << shift) - 1u);
-        uint32_t mid = 1u << (shift - 1);
-        if (rem > mid || (rem == mid && (half & 1u))) ++half;
-        return (uint16_t)(sign | half);
-    }
-    uint32_t half = ((uint32_t)e << 10) | (man >> 13);
-    uint32_t rem = man & 0x1FFFu;
-    if (rem > 0x1000u || (rem == 0x1000u && (half & 1u))) ++half;   // may carry into inf
-    return (uint16_t)(sign | half);
-}
-
-uint16_t f32_to_bf16_rne(float x) {
-    uint32_t u;
-    memcpy(&u, &x, 4);
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x7FFFFFu)) return (uint16_t)((u >> 16) | 0x40u);
-    uint32_t lsb = (u >> 16) & 1u;
-    return (uint16_t)((u + 0x7FFFu + lsb) >> 16);
-}
-
 int row_bytes(int storage, int K);   // octree_query.hip
 
 // ------------------------------------------------------------ validation
+lq_status check_octree_scalars(float l_max, float sigma_min, float alpha_max) {
+    if (!(l_max > 0.0f) || !isfinite(l_max)) return fail(LQ_ERR_FORMAT, "l_max must be finite and > 0");
+    if (!isfinite(sigma_min) || !(alpha_max > 0.0f) || !(alpha_max <= 1.0f))
+        return fail(LQ_ERR_FORMAT, "sigma_min must be finite and alpha_max in (0, 1]");
+    return LQ_OK;
+}
+
 // On success, *bfs (if given) receives the nodes in breadth-first order.
 static lq_status validate_desc(const lq_octree_desc *d, std::vector<int32_t> *bfs = nullptr) {
     if (!d) return fail(LQ_ERR_INVALID_ARG, "descriptor is NULL");
@@ -85,9 +59,8 @@ static lq_status validate_desc(const lq_octree_desc *d, std::vector<int32_t> *bf
     if (d->n_leaves < 0) return fail(LQ_ERR_FORMAT, "n_leaves must be >= 0");
     if (!d->child) return fail(LQ_ERR_INVALID_ARG, "child table is NULL");
     if (d->n_leaves > 0 && (!d->sigma || !d->sh)) return fail(LQ_ERR_INVALID_ARG, "sigma/sh is NULL");
-    if (!(d->l_max > 0.0f) || !isfinite(d->l_max)) return fail(LQ_ERR_FORMAT, "l_max must be finite and > 0");
-    if (!isfinite(d->sigma_min) || !(d->alpha_max > 0.0f) || !(d->alpha_max <= 1.0f))
-        return fail(LQ_ERR_FORMAT, "sigma_min must be finite and alpha_max in (0, 1]");
+    const lq_status st = check_octree_scalars(d->l_max, d->sigma_min, d->alpha_max);
+    if (st != LQ_OK) return st;
     // the child table must be a tree with leaves exactly one level above max depth
     const int D = d->max_depth;
     std::vector<uint8_t> seen_node(d->n_nodes, 0);
@@ -123,31 +96,59 @@ static lq_status validate_desc(const lq_octree_desc *d, std::vector<int32_t> *bf
     return LQ_OK;
 }
 
+// ---------------------------------------------------------- device tables
 // Dense top grid of a child table (see DevTree::top): the descent from the
 // root along every cell of level kTopLevel; cells are indexed z, y, x.
-static std::vector<int32_t> top_grid(const int32_t *table, int depth) {
-    std::vector<int32_t> g;
-    if (depth <= kTopLevel) return g;
-    const int R = 1 << kTopLevel;
-    g.resize(kTopCells);
-    for (int z = 0; z < R; ++z)
-        for (int y = 0; y < R; ++y)
-            for (int x = 0; x < R; ++x) {
-                int32_t node = 0, e = 0;
-                for (int level = 0; level < kTopLevel; ++level) {
-                    const int b = kTopLevel - 1 - level;
-                    const int oct = ((x >> b) & 1) | (((y >> b) & 1) << 1) | (((z >> b) & 1) << 2);
-                    const int32_t c = table[(size_t)node * 8 + oct];
-                    if (c <= 0) {   // leaves sit at max depth > kTopLevel: c is empty
-                        e = -(level + 1);
-                        break;
-                    }
-                    node = c;
-                    e = c;
-                }
-                g[((size_t)z * R + y) * R + x] = e;
-            }
-    return g;
+static __global__ void k_top_grid(const int32_t *table, int32_t *grid) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, m = (1 << kTopLevel) - 1;
+    if (i >= kTopCells) return;
+    const int x = i & m, y = (i >> kTopLevel) & m, z = i >> (2 * kTopLevel);
+    int32_t node = 0;
+    for (int level = 0; level < kTopLevel; ++level) {
+        const int b = kTopLevel - 1 - level;
+        const int oct = ((x >> b) & 1) | (((y >> b) & 1) << 1) | (((z >> b) & 1) << 2);
+        const int32_t c = table[(size_t)node * 8 + oct];
+        if (c <= 0) {   // leaves sit at max depth > kTopLevel: c is empty
+            grid[i] = -(level + 1);
+            return;
+        }
+        node = c;
+    }
+    grid[i] = node;
+}
+
+// Leaf rows (DevTree::rows) in the storage type, one thread per 4-byte word:
+// a word's values are read from sigma and sh, the padding is 0.  Streams its
+// input and output once.
+static __global__ void k_rows(const float *sigma, const float *sh, int64_t n, int sh_per_leaf, int row_words,
+                              int storage, uint32_t *rows) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * row_words) return;
+    const int64_t leaf = i / row_words;
+    const int word = (int)(i - leaf * row_words);
+    const auto value = [&](int j) {
+        return j == 0 ? sigma[leaf] : j <= sh_per_leaf ? sh[leaf * sh_per_leaf + (j - 1)] : 0.0f;
+    };
+    const auto half = [&](int j) -> uint32_t {
+        const float v = value(j);
+        return storage == LQ_F16 ? f32_to_f16_rne(v) : f32_to_bf16_rne(v);
+    };
+    rows[i] = storage == LQ_F32 ? __builtin_bit_cast(uint32_t, value(word)) : half(2 * word) | half(2 * word + 1) << 16;
+}
+
+// the rows' densities and coefficients back as float32, one thread per value
+static __global__ void k_unpack_rows(const void *rows, int64_t n, int sh_per_leaf, int row_elems, int storage,
+                                     float *sigma, float *sh) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int per = sh_per_leaf + 1;
+    if (i >= n * per) return;
+    const int64_t leaf = i / per, at = leaf * row_elems;
+    const int j = (int)(i - leaf * per);
+    const uint32_t bits = storage == LQ_F32 ? static_cast<const uint32_t *>(rows)[at + j]
+                                            : static_cast<const uint16_t *>(rows)[at + j];
+    const float v = stored_to_f32(storage, bits);
+    if (j == 0) sigma[leaf] = v;
+    else sh[leaf * sh_per_leaf + (j - 1)] = v;
 }
 
 // Child table without the leaves for which keep_leaf() is false and without
@@ -184,6 +185,72 @@ static std::vector<int32_t> prune_tree(const lq_octree_desc *d, const std::vecto
     return out;
 }
 
+lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree **out) {
+    lq_octree *t = new (std::nothrow) lq_octree();
+    if (!t) {
+        (void)hipFree(p.child);
+        (void)hipFree(p.child_skip);
+        return fail(LQ_ERR_OOM, "host allocation failed");
+    }
+    const int K = (p.sh_degree + 1) * (p.sh_degree + 1);
+    const int esz = storage == LQ_F32 ? 4 : 2;
+    const int rb = row_bytes(storage, K);
+    const bool grids = p.max_depth > kTopLevel;
+    const size_t top_bytes = grids ? (size_t)2 * kTopCells * 4 : 0;
+    const size_t row_total = p.n_leaves ? (size_t)p.n_leaves * rb : 64;
+    t->device = device;
+    t->d_child = p.child;
+    t->d_child_skip = p.child_skip;
+    t->d_top = nullptr;
+    t->d_bricks = nullptr;
+    t->d_rows = nullptr;
+    if ((grids && hipMalloc((void **)&t->d_top, top_bytes) != hipSuccess) ||
+        hipMalloc(&t->d_rows, row_total) != hipSuccess) {
+        (void)hipGetLastError();
+        lq_free_octree(t);
+        return fail(LQ_ERR_OOM, "device allocation of the tree tables failed");
+    }
+    hipStream_t s = nullptr;
+    if (grids) {
+        hipLaunchKernelGGL(k_top_grid, dim3(kTopCells / 256), dim3(256), 0, s, p.child, t->d_top);
+        hipLaunchKernelGGL(k_top_grid, dim3(kTopCells / 256), dim3(256), 0, s, p.child_skip, t->d_top + kTopCells);
+    }
+    if (p.n_leaves) {
+        const int64_t words = (int64_t)p.n_leaves * (rb / 4);
+        hipLaunchKernelGGL(k_rows, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, p.sigma, p.sh,
+                           (int64_t)p.n_leaves, 3 * K, rb / 4, storage, static_cast<uint32_t *>(t->d_rows));
+    }
+    DevTree &dt = t->t;
+    dt.child = t->d_child;
+    dt.child_skip = t->d_child_skip;
+    dt.top = grids ? t->d_top : nullptr;
+    dt.top_skip = grids ? t->d_top + kTopCells : nullptr;
+    dt.rows = t->d_rows;
+    dt.depth = p.max_depth;
+    dt.sh_degree = p.sh_degree;
+    dt.K = K;
+    dt.storage = storage;
+    dt.n_nodes = p.n_nodes;
+    dt.n_leaves = p.n_leaves;
+    dt.row_elems = rb / esz;
+    dt.l_max = p.l_max;
+    dt.sigma_min = p.sigma_min;
+    dt.alpha_max = p.alpha_max;
+    size_t brick_bytes = 0;
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+        e = build_bricks(t->d_child_skip, p.max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        lq_free_octree(t);
+        return e == hipErrorOutOfMemory ? fail(LQ_ERR_OOM, "device allocation of the brick tables failed")
+                                        : hip_fail(e, "building the tree's tables");
+    }
+    t->bytes = (int64_t)((size_t)p.n_nodes * 32 + (size_t)p.n_skip_nodes * 32 + top_bytes + brick_bytes + row_total);
+    *out = t;
+    return LQ_OK;
+}
+
 }  // namespace lq
 
 using namespace lq;
@@ -210,105 +277,48 @@ lq_status lq_load_octree_desc(const lq_octree_desc *desc, int storage, int devic
     if (device < 0 || device >= ndev) return fail(LQ_ERR_INVALID_ARG, "device index out of range");
     if ((e = hipSetDevice(device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
 
-    const int K = (desc->sh_degree + 1) * (desc->sh_degree + 1);
-    const int esz = storage == LQ_F32 ? 4 : 2;
-    const int rb = row_bytes(storage, K);
-    const int64_t nl = desc->n_leaves;
-    std::vector<uint8_t> rows((size_t)nl * rb, 0);
-    for (int64_t i = 0; i < nl; ++i) {
-        uint8_t *row = rows.data() + (size_t)i * rb;
-        for (int j = 0; j < 1 + 3 * K; ++j) {
-            float v = j == 0 ? desc->sigma[i] : desc->sh[(size_t)i * 3 * K + (j - 1)];
-            if (storage == LQ_F32) {
-                memcpy(row + 4 * j, &v, 4);
-            } else {
-                uint16_t b = storage == LQ_F16 ? f32_to_f16_rne(v) : f32_to_bf16_rne(v);
-                memcpy(row + esz * j, &b, 2);
-            }
-        }
-    }
-    // density as stored (after rounding), compared like the kernel does
-    auto stored_sigma = [&](int64_t leaf) -> float {
-        if (storage == LQ_F32) return desc->sigma[leaf];
-        uint16_t b;
-        memcpy(&b, rows.data() + (size_t)leaf * rb, 2);
-        if (storage == LQ_BF16) {
-            uint32_t u = (uint32_t)b << 16;
-            float f;
-            memcpy(&f, &u, 4);
-            return f;
-        }
-        return (float)__builtin_bit_cast(_Float16, b);
-    };
-    const float smin = desc->sigma_min;
-    std::vector<int32_t> skip = prune_tree(desc, bfs, [&](int64_t leaf) { return stored_sigma(leaf) >= smin; });
-
-    lq_octree *t = new (std::nothrow) lq_octree();
-    if (!t) return fail(LQ_ERR_OOM, "host allocation failed");
-    t->device = device;
-    const size_t child_bytes = (size_t)desc->n_nodes * 32;
-    const size_t skip_bytes = skip.size() * 4;
-    const size_t row_total = rows.size() ? rows.size() : 64;
-    std::vector<int32_t> tops = top_grid(desc->child, desc->max_depth);
-    const std::vector<int32_t> top_skip = top_grid(skip.data(), desc->max_depth);
-    tops.insert(tops.end(), top_skip.begin(), top_skip.end());
-    const size_t top_bytes = tops.size() * 4;
-    t->d_child = nullptr;
-    t->d_child_skip = nullptr;
-    t->d_top = nullptr;
-    t->d_bricks = nullptr;
-    t->d_rows = nullptr;
+    const int64_t nl = desc->n_leaves, sh_per_leaf = 3 * (desc->sh_degree + 1) * (desc->sh_degree + 1);
+    const std::vector<int32_t> skip = prune_tree(desc, bfs, [&](int64_t leaf) {
+        // density as stored (after rounding), compared like the kernel does
+        return as_stored(storage, desc->sigma[leaf]) >= desc->sigma_min;
+    });
+    OctreeParts p{};
+    p.max_depth = desc->max_depth;
+    p.sh_degree = desc->sh_degree;
+    p.n_nodes = desc->n_nodes;
+    p.n_skip_nodes = (int32_t)(skip.size() / 8);
+    p.n_leaves = desc->n_leaves;
+    p.l_max = desc->l_max;
+    p.sigma_min = desc->sigma_min;
+    p.alpha_max = desc->alpha_max;
+    const size_t child_bytes = (size_t)desc->n_nodes * 32, skip_bytes = skip.size() * 4;
+    float *leaves = nullptr;   // densities, then coefficients
     auto release = [&]() {
-        (void)hipFree(t->d_child);
-        (void)hipFree(t->d_child_skip);
-        (void)hipFree(t->d_top);
-        (void)hipFree(t->d_bricks);
-        (void)hipFree(t->d_rows);
-        delete t;
+        (void)hipFree(p.child);
+        (void)hipFree(p.child_skip);
+        (void)hipFree(leaves);
     };
-    if (hipMalloc((void **)&t->d_child, child_bytes) != hipSuccess ||
-        hipMalloc((void **)&t->d_child_skip, skip_bytes) != hipSuccess ||
-        (top_bytes && hipMalloc((void **)&t->d_top, top_bytes) != hipSuccess) ||
-        hipMalloc(&t->d_rows, row_total) != hipSuccess) {
+    if (hipMalloc((void **)&p.child, child_bytes) != hipSuccess ||
+        hipMalloc((void **)&p.child_skip, skip_bytes) != hipSuccess ||
+        (nl && hipMalloc((void **)&leaves, (size_t)nl * (1 + sh_per_leaf) * 4) != hipSuccess)) {
         (void)hipGetLastError();
         release();
         return fail(LQ_ERR_OOM, "device allocation of the tree tables failed");
     }
-    e = hipMemcpy(t->d_child, desc->child, child_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(t->d_child_skip, skip.data(), skip_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess && top_bytes) e = hipMemcpy(t->d_top, tops.data(), top_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess && rows.size()) e = hipMemcpy(t->d_rows, rows.data(), rows.size(), hipMemcpyHostToDevice);
+    e = hipMemcpy(p.child, desc->child, child_bytes, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(p.child_skip, skip.data(), skip_bytes, hipMemcpyHostToDevice);
+    if (e == hipSuccess && nl) e = hipMemcpy(leaves, desc->sigma, (size_t)nl * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess && nl)
+        e = hipMemcpy(leaves + nl, desc->sh, (size_t)nl * sh_per_leaf * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         release();
         return hip_fail(e, "uploading the tree");
     }
-    DevTree &dt = t->t;
-    size_t brick_bytes = 0;
-    e = build_bricks(t->d_child_skip, desc->max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        release();
-        return e == hipErrorOutOfMemory ? fail(LQ_ERR_OOM, "device allocation of the brick tables failed")
-                                        : hip_fail(e, "building the brick tables");
-    }
-    t->bytes = (int64_t)(child_bytes + skip_bytes + top_bytes + brick_bytes + row_total);
-    dt.child = t->d_child;
-    dt.child_skip = t->d_child_skip;
-    dt.top = top_bytes ? t->d_top : nullptr;
-    dt.top_skip = top_bytes ? t->d_top + kTopCells : nullptr;
-    dt.rows = t->d_rows;
-    dt.depth = desc->max_depth;
-    dt.sh_degree = desc->sh_degree;
-    dt.K = K;
-    dt.storage = storage;
-    dt.n_nodes = desc->n_nodes;
-    dt.n_leaves = desc->n_leaves;
-    dt.row_elems = rb / esz;
-    dt.l_max = desc->l_max;
-    dt.sigma_min = desc->sigma_min;
-    dt.alpha_max = desc->alpha_max;
-    *out = t;
-    return LQ_OK;
+    p.sigma = leaves;
+    p.sh = leaves + nl;
+    st = make_octree(p, storage, device, out);
+    (void)hipFree(leaves);
+    return st;
 }
 
 lq_status lq_load_octree(const char *path, int storage, int device, lq_octree **out) {
@@ -380,35 +390,21 @@ lq_status lq_octree_download(const lq_octree *t, int32_t *child, float *sigma, f
     const DevTree &dt = t->t;
     if (child && (e = hipMemcpy(child, t->d_child, (size_t)dt.n_nodes * 32, hipMemcpyDeviceToHost)) != hipSuccess)
         return hip_fail(e, "reading the child table");
-    if (!sigma && !sh) return LQ_OK;
-    const int esz = dt.storage == LQ_F32 ? 4 : 2;
-    const size_t rb = (size_t)dt.row_elems * esz;
-    std::vector<uint8_t> rows((size_t)dt.n_leaves * rb);
-    if (!rows.empty() && (e = hipMemcpy(rows.data(), t->d_rows, rows.size(), hipMemcpyDeviceToHost)) != hipSuccess)
-        return hip_fail(e, "reading the leaf rows");
-    auto value = [&](const uint8_t *row, int j) -> float {
-        if (dt.storage == LQ_F32) {
-            float f;
-            memcpy(&f, row + 4 * j, 4);
-            return f;
-        }
-        uint16_t b;
-        memcpy(&b, row + 2 * j, 2);
-        if (dt.storage == LQ_BF16) {
-            const uint32_t u = (uint32_t)b << 16;
-            float f;
-            memcpy(&f, &u, 4);
-            return f;
-        }
-        return (float)__builtin_bit_cast(_Float16, b);
-    };
-    for (int64_t i = 0; i < dt.n_leaves; ++i) {
-        const uint8_t *row = rows.data() + (size_t)i * rb;
-        if (sigma) sigma[i] = value(row, 0);
-        if (sh)
-            for (int j = 0; j < 3 * dt.K; ++j) sh[(size_t)i * 3 * dt.K + j] = value(row, 1 + j);
+    if ((!sigma && !sh) || dt.n_leaves == 0) return LQ_OK;
+    const size_t n = (size_t)dt.n_leaves;
+    const int sh_per_leaf = 3 * dt.K;
+    float *vals = nullptr;   // densities, then coefficients
+    if (hipMalloc((void **)&vals, n * (1 + sh_per_leaf) * 4) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(LQ_ERR_OOM, "device scratch of the download");
     }
-    return LQ_OK;
+    hipLaunchKernelGGL(k_unpack_rows, dim3((unsigned)((n * (1 + sh_per_leaf) + 255) / 256)), dim3(256), 0, nullptr,
+                       dt.rows, (int64_t)n, sh_per_leaf, dt.row_elems, dt.storage, vals, vals + n);
+    e = hipGetLastError();
+    if (e == hipSuccess && sigma) e = hipMemcpy(sigma, vals, n * 4, hipMemcpyDeviceToHost);
+    if (e == hipSuccess && sh) e = hipMemcpy(sh, vals + n, n * sh_per_leaf * 4, hipMemcpyDeviceToHost);
+    (void)hipFree(vals);
+    return e == hipSuccess ? LQ_OK : hip_fail(e, "reading the leaf rows");
 }
 
 lq_status lq_octree_info(const lq_octree *t, int64_t *device_bytes, int32_t *n_nodes, int32_t *n_leaves,

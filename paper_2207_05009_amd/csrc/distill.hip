@@ -46,6 +46,7 @@
 #include <vector>
 
 #include "lq_internal.h"
+#include "storage.h"
 
 namespace lq {
 namespace {
@@ -420,12 +421,32 @@ __global__ void k_check_codes(const uint32_t *codes, uint64_t n, uint64_t limit,
     if (codes[i] >= limit || (i > 0 && codes[i] <= codes[i - 1])) atomicOr(bad, 1u);
 }
 
+// leaves: the leaf index of each kid, for the leaves' level (null: a level of nodes)
 __global__ void k_child_write(const uint32_t *kids, uint64_t n, const uint32_t *pidx, int32_t base_parent,
-                              int32_t base_kids, int leaves, int32_t *child) {
+                              int32_t base_kids, const uint32_t *leaves, int32_t *child) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int32_t v = leaves ? -(int32_t)(i + 1) : base_kids + (int32_t)i;
+    const int32_t v = leaves ? -(int32_t)(leaves[i] + 1u) : base_kids + (int32_t)i;
     child[(uint64_t)(base_parent + (int32_t)pidx[i]) * 8u + (kids[i] & 7u)] = v;
+}
+
+// leaves that the sigma_min skip keeps, compared as stored
+__global__ void k_kept_leaves(const float *sigma, uint64_t n, int storage, float sigma_min, uint32_t *kept) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) kept[i] = as_stored(storage, sigma[i]) >= sigma_min ? 1u : 0u;
+}
+
+__global__ void k_compact_leaves(const uint32_t *codes, uint64_t n, const uint32_t *kept, const uint32_t *pos,
+                                 uint32_t *out_codes, uint32_t *out_leaf) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n || !kept[i]) return;
+    out_codes[pos[i]] = codes[i];
+    out_leaf[pos[i]] = (uint32_t)i;
+}
+
+__global__ void k_iota(uint32_t *p, uint64_t n) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = (uint32_t)i;
 }
 
 __global__ void k_fill_i32(int32_t *p, uint64_t n, int32_t v) {
@@ -441,19 +462,34 @@ lq_status dhip(hipError_t e, const char *what) {
     return dfail(LQ_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// Device buffers freed at scope exit (after the stream is synchronised).
+// Device scratch, freed at scope exit (after the stream is synchronised).
+// Arrays are cut from blocks of at least 16 MiB: an allocation per array (56
+// for a depth-8 tree) took longer than the kernels between them.
 struct DevBufs {
+    static constexpr size_t kBlockBytes = (size_t)16 << 20;
     std::vector<void *> p;
+    char *at = nullptr;
+    size_t left = 0;
     ~DevBufs() {
         for (void *q : p) (void)hipFree(q);
     }
     template <class T>
     hipError_t alloc(T **out, size_t count) {
-        void *q = nullptr;
-        hipError_t e = hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T));
-        if (e == hipSuccess) p.push_back(q);
-        *out = static_cast<T *>(q);
-        return e;
+        const size_t bytes = (std::max<size_t>(count, 1) * sizeof(T) + 255) & ~(size_t)255;
+        *out = nullptr;
+        if (bytes > left) {
+            void *q = nullptr;
+            const size_t block = std::max(bytes, kBlockBytes);
+            const hipError_t e = hipMalloc(&q, block);
+            if (e != hipSuccess) return e;
+            p.push_back(q);
+            at = static_cast<char *>(q);
+            left = block;
+        }
+        *out = reinterpret_cast<T *>(at);
+        at += bytes;
+        left -= bytes;
+        return hipSuccess;
     }
 };
 
@@ -471,6 +507,70 @@ hipError_t scan_u32(const uint32_t *v, uint64_t n, uint32_t *out, uint32_t *tota
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipMemcpyAsync(total_host, tot, 4, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
     return hipStreamSynchronize(s);
+}
+
+constexpr unsigned kBuildThreads = 256;
+dim3 build_grid(uint64_t m) {
+    return dim3((unsigned)std::max<uint64_t>(1, (m + kBuildThreads - 1) / kBuildThreads));
+}
+
+// Child table (hipMalloc, the caller's) of the tree whose leaves are n
+// ascending codes with leaf indices leaf[0..n): levels bottom-up, then the
+// slots, breadth-first, Morton order within a level.
+lq_status build_child(int max_depth, const uint32_t *codes, const uint32_t *leaf, uint64_t n, DevBufs &b,
+                      hipStream_t s, int32_t **child, int64_t *n_nodes_out) {
+    hipError_t e;
+    *child = nullptr;
+    std::vector<const uint32_t *> level(max_depth + 1, nullptr);
+    std::vector<uint32_t *> pidx(max_depth + 1, nullptr);
+    std::vector<uint64_t> count(max_depth + 1, 0);
+    level[max_depth] = codes;
+    count[max_depth] = n;
+    for (int l = max_depth - 1; l >= 0; --l) {
+        const uint64_t m = count[l + 1];
+        if (m == 0) continue;
+        uint32_t *head, *pos, *par, *pi;
+        if ((e = b.alloc(&head, m)) != hipSuccess || (e = b.alloc(&pos, m)) != hipSuccess ||
+            (e = b.alloc(&par, m)) != hipSuccess || (e = b.alloc(&pi, m)) != hipSuccess)
+            return dfail(LQ_ERR_OOM, "device scratch of the octree build");
+        hipLaunchKernelGGL(k_parent_heads, build_grid(m), dim3(kBuildThreads), 0, s, level[l + 1], m, head);
+        uint32_t total = 0;
+        if ((e = scan_u32(head, m, pos, &total, b, s)) != hipSuccess) return dhip(e, "scanning a level");
+        hipLaunchKernelGGL(k_parent_compact, build_grid(m), dim3(kBuildThreads), 0, s, level[l + 1], m, head, pos, par,
+                           pi);
+        level[l] = par;
+        pidx[l + 1] = pi;
+        count[l] = total;
+    }
+    // the root always exists (level 0 holds code 0 when any leaf exists)
+    count[0] = 1;
+    std::vector<int64_t> base(max_depth + 1, 0);
+    int64_t n_nodes = 0;
+    for (int l = 0; l < max_depth; ++l) {
+        base[l] = n_nodes;
+        n_nodes += (int64_t)count[l];
+    }
+    if (n_nodes >= (1 << 29)) return dfail(LQ_ERR_UNSUPPORTED, "too many nodes");
+    const uint64_t slots = (uint64_t)n_nodes * 8;
+    if (hipMalloc((void **)child, slots * 4) != hipSuccess) {
+        (void)hipGetLastError();
+        *child = nullptr;
+        return dfail(LQ_ERR_OOM, "device child table");
+    }
+    hipLaunchKernelGGL(k_fill_i32, build_grid(slots), dim3(kBuildThreads), 0, s, *child, slots, 0);
+    for (int l = 0; l < max_depth; ++l) {
+        const uint64_t m = count[l + 1];
+        if (m == 0 || !pidx[l + 1]) continue;
+        hipLaunchKernelGGL(k_child_write, build_grid(m), dim3(kBuildThreads), 0, s, level[l + 1], m, pidx[l + 1],
+                           (int32_t)base[l], (int32_t)base[l + 1], l + 1 == max_depth ? leaf : nullptr, *child);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) {
+        (void)hipFree(*child);
+        *child = nullptr;
+        return dhip(e, "launching the octree build");
+    }
+    *n_nodes_out = n_nodes;
+    return LQ_OK;
 }
 
 lq_status field_args(const lq_field_desc *fd, int depth, float prune_sigma, FieldArgs &f) {
@@ -662,80 +762,52 @@ lq_status lq_octree_from_leaves(int32_t max_depth, int32_t sh_degree, const uint
     hipStream_t s = nullptr;
     DevBufs b;
     const uint64_t n = (uint64_t)n_leaves;
-    const unsigned tb = 256;
-    auto grid = [&](uint64_t m) { return dim3((unsigned)std::max<uint64_t>(1, (m + tb - 1) / tb)); };
     if (n > 0) {
         uint32_t *bad;
         if ((e = b.alloc(&bad, 1)) != hipSuccess) return dfail(LQ_ERR_OOM, "device scratch");
         uint32_t hbad = 0;
         if ((e = hipMemcpy(bad, &hbad, 4, hipMemcpyHostToDevice)) != hipSuccess) return dhip(e, "scratch");
-        hipLaunchKernelGGL(k_check_codes, grid(n), dim3(tb), 0, s, codes, n, 1ull << (3 * max_depth), bad);
+        hipLaunchKernelGGL(k_check_codes, build_grid(n), dim3(kBuildThreads), 0, s, codes, n, 1ull << (3 * max_depth),
+                           bad);
         if ((e = hipMemcpy(&hbad, bad, 4, hipMemcpyDeviceToHost)) != hipSuccess) return dhip(e, "checking codes");
         if (hbad) return dfail(LQ_ERR_FORMAT, "codes must be strictly ascending Morton codes below 8^max_depth");
     }
-    // levels bottom-up: level[max_depth] = the leaves' codes
-    std::vector<const uint32_t *> level(max_depth + 1, nullptr);
-    std::vector<uint32_t *> pidx(max_depth + 1, nullptr);
-    std::vector<uint64_t> count(max_depth + 1, 0);
-    level[max_depth] = codes;
-    count[max_depth] = n;
-    for (int l = max_depth - 1; l >= 0; --l) {
-        const uint64_t m = count[l + 1];
-        if (m == 0) {
-            count[l] = l == 0 ? 1 : 0;
-            continue;
-        }
-        uint32_t *head, *pos, *par, *pi;
-        if ((e = b.alloc(&head, m)) != hipSuccess || (e = b.alloc(&pos, m)) != hipSuccess ||
-            (e = b.alloc(&par, m)) != hipSuccess || (e = b.alloc(&pi, m)) != hipSuccess)
-            return dfail(LQ_ERR_OOM, "device scratch of the octree build");
-        hipLaunchKernelGGL(k_parent_heads, grid(m), dim3(tb), 0, s, level[l + 1], m, head);
-        uint32_t total = 0;
-        if ((e = scan_u32(head, m, pos, &total, b, s)) != hipSuccess) return dhip(e, "scanning a level");
-        hipLaunchKernelGGL(k_parent_compact, grid(m), dim3(tb), 0, s, level[l + 1], m, head, pos, par, pi);
-        level[l] = par;
-        pidx[l + 1] = pi;
-        count[l] = total;
+    if (storage != LQ_F32 && storage != LQ_F16 && storage != LQ_BF16)
+        return dfail(LQ_ERR_INVALID_ARG, "storage must be LQ_F32, LQ_F16 or LQ_BF16");
+    if ((st = check_octree_scalars(l_max, sigma_min, alpha_max)) != LQ_OK) return st;
+    // the full table, and the one without the leaves below sigma_min: the
+    // same build over the leaves kept
+    uint32_t *leaf, *kept, *pos, *kept_codes, *kept_leaf;
+    if ((e = b.alloc(&leaf, n)) != hipSuccess || (e = b.alloc(&kept, n)) != hipSuccess ||
+        (e = b.alloc(&pos, n)) != hipSuccess || (e = b.alloc(&kept_codes, n)) != hipSuccess ||
+        (e = b.alloc(&kept_leaf, n)) != hipSuccess)
+        return dfail(LQ_ERR_OOM, "device scratch of the octree build");
+    uint32_t n_kept = 0;
+    if (n > 0) {
+        hipLaunchKernelGGL(k_iota, build_grid(n), dim3(kBuildThreads), 0, s, leaf, n);
+        hipLaunchKernelGGL(k_kept_leaves, build_grid(n), dim3(kBuildThreads), 0, s, sigma, n, storage, sigma_min, kept);
+        if ((e = scan_u32(kept, n, pos, &n_kept, b, s)) != hipSuccess) return dhip(e, "scanning the leaves");
+        hipLaunchKernelGGL(k_compact_leaves, build_grid(n), dim3(kBuildThreads), 0, s, codes, n, kept, pos, kept_codes,
+                           kept_leaf);
     }
-    // the root always exists (level 0 holds code 0 when any leaf exists)
-    count[0] = 1;
-    std::vector<int64_t> base(max_depth + 1, 0);
-    int64_t n_nodes = 0;
-    for (int l = 0; l < max_depth; ++l) {
-        base[l] = n_nodes;
-        n_nodes += (int64_t)count[l];
+    OctreeParts p{};
+    int64_t n_nodes = 0, n_skip = 0;
+    if ((st = build_child(max_depth, codes, leaf, n, b, s, &p.child, &n_nodes)) != LQ_OK) return st;
+    if ((st = build_child(max_depth, kept_codes, kept_leaf, n_kept, b, s, &p.child_skip, &n_skip)) != LQ_OK) {
+        (void)hipFree(p.child);
+        return st;
     }
-    if (n_nodes >= (1 << 29)) return dfail(LQ_ERR_UNSUPPORTED, "too many nodes");
-    int32_t *child;
-    if ((e = b.alloc(&child, (size_t)n_nodes * 8)) != hipSuccess) return dfail(LQ_ERR_OOM, "device child table");
-    hipLaunchKernelGGL(k_fill_i32, grid((uint64_t)n_nodes * 8), dim3(tb), 0, s, child, (uint64_t)n_nodes * 8, 0);
-    for (int l = 0; l < max_depth; ++l) {
-        const uint64_t m = count[l + 1];
-        if (m == 0 || !pidx[l + 1]) continue;
-        hipLaunchKernelGGL(k_child_write, grid(m), dim3(tb), 0, s, level[l + 1], m, pidx[l + 1], (int32_t)base[l],
-                           (int32_t)base[l + 1], l + 1 == max_depth ? 1 : 0, child);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return dhip(e, "launching the octree build");
-    // the device table and leaves become an octree through the loader
-    // (validation, storage conversion, the sigma_min-pruned table, top grids)
-    std::vector<int32_t> hchild((size_t)n_nodes * 8);
-    std::vector<float> hsig(n), hsh(n * 3 * K);
-    if ((e = hipMemcpy(hchild.data(), child, hchild.size() * 4, hipMemcpyDeviceToHost)) != hipSuccess ||
-        (n && (e = hipMemcpy(hsig.data(), sigma, n * 4, hipMemcpyDeviceToHost)) != hipSuccess) ||
-        (n && (e = hipMemcpy(hsh.data(), sh, n * 12 * K, hipMemcpyDeviceToHost)) != hipSuccess))
-        return dhip(e, "reading the built octree");
-    lq_octree_desc d;
-    d.max_depth = max_depth;
-    d.sh_degree = sh_degree;
-    d.n_nodes = (int32_t)n_nodes;
-    d.n_leaves = (int32_t)n;
-    d.l_max = l_max;
-    d.sigma_min = sigma_min;
-    d.alpha_max = alpha_max;
-    d.child = hchild.data();
-    d.sigma = hsig.data();
-    d.sh = hsh.data();
-    return lq_load_octree_desc(&d, storage, device, out);
+    p.max_depth = max_depth;
+    p.sh_degree = sh_degree;
+    p.n_nodes = (int32_t)n_nodes;
+    p.n_skip_nodes = (int32_t)n_skip;
+    p.n_leaves = (int32_t)n;
+    p.l_max = l_max;
+    p.sigma_min = sigma_min;
+    p.alpha_max = alpha_max;
+    p.sigma = sigma;
+    p.sh = sh;
+    return make_octree(p, storage, device, out);
 }
 
 }  // extern "C"

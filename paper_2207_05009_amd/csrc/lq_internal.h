@@ -130,9 +130,18 @@ hipError_t launch_query_multi(int storage, int sh_degree, const DevTree *trees, 
 hipError_t build_bricks(const int32_t *child_skip, int depth, uint32_t **buf, size_t *bytes, const uint32_t **brick_top,
                         const uint32_t **bricks);
 
-// FP32 -> storage conversions used by the loader (round to nearest even)
-uint16_t f32_to_f16_rne(float x);
-uint16_t f32_to_bf16_rne(float x);
+// An octree on `device` (current) from device tables: its child tables (which
+// it takes over) and its leaves' densities and coefficients (read during the
+// call).  On failure the child tables are freed.  Synchronous.
+struct OctreeParts {
+    int32_t max_depth, sh_degree, n_nodes, n_skip_nodes, n_leaves;
+    float l_max, sigma_min, alpha_max;
+    int32_t *child, *child_skip;
+    const float *sigma, *sh;
+};
+lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree **out);
+// the scalars of a tree: LQ_OK, or the error a loader returns for them
+lq_status check_octree_scalars(float l_max, float sigma_min, float alpha_max);
 
 void set_error(const std::string &msg);
 
