@@ -43,6 +43,7 @@
 #include <algorithm>
 #include <cmath>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lq_internal.h"
@@ -92,16 +93,18 @@ __device__ inline bool in_shell_f64(const FieldArgs &f, int j, double x, double 
     return fabs(dist - f.dsr[j]) < f.dhalf_width;
 }
 
+__device__ inline bool in_one_shell(const FieldArgs &f, int j, float xf, float yf, float zf, double x, double y,
+                                    double z) {
+    const float dx = (xf - f.sx[j]) - f.sxl[j], dy = (yf - f.sy[j]) - f.syl[j], dz = (zf - f.sz[j]) - f.szl[j];
+    const float dist = __builtin_amdgcn_sqrtf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
+    const float m = fabsf(dist - f.sr[j]) - f.half_width;
+    return fabsf(m) > 1e-5f ? m < 0.0f : in_shell_f64(f, j, x, y, z);
+}
+
 __device__ inline bool in_shell(const FieldArgs &f, double x, double y, double z) {
     const float xf = (float)x, yf = (float)y, zf = (float)z;
     bool in = false;
-    for (int j = 0; j < f.ns; ++j) {
-        const float dx = (xf - f.sx[j]) - f.sxl[j], dy = (yf - f.sy[j]) - f.syl[j], dz = (zf - f.sz[j]) - f.szl[j];
-        const float dist = __builtin_amdgcn_sqrtf(fmaf(dz, dz, fmaf(dy, dy, dx * dx)));
-        const float m = fabsf(dist - f.sr[j]) - f.half_width;
-        if (fabsf(m) > 1e-5f) in = in || m < 0.0f;
-        else in = in || in_shell_f64(f, j, x, y, z);
-    }
+    for (int j = 0; j < f.ns; ++j) in = in || in_one_shell(f, j, xf, yf, zf, x, y, z);
     return in;
 }
 
@@ -221,14 +224,15 @@ __global__ __launch_bounds__(kWordsPerChunk) void k_centre_compact(const unsigne
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC 2011): 10 rounds of two
 // 32x32 -> 64-bit multiplications with the key bumped by the Weyl constants.
 // Each product is one 64-bit multiply (a single v_mad_u64_u32).
-__device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
-                                     uint32_t out[4]) {
+template <int ROUNDS>
+__device__ inline void philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
+                                         uint32_t out[4]) {
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
-        c0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+        c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);   // three-way xor
         c1 = (uint32_t)p1;
-        c2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, 0x96);
         c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
@@ -240,10 +244,7 @@ __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint
 }
 
 // One lane per kept voxel i < n: the means over n_samples positions.
-// sh_out[i][c][k]; hi [nb][3][K - 1] (device, FP64).  rec: NB records of
-// four doubles (centre, -log2(e) / (2 r^2)), then NB float4 records
-// (amplitude, radiance); those past nb are padded so that their terms
-// vanish (exp2 of a huge negative argument is exactly 0).
+// sh_out[i][c][k]; hi [nb][3][K - 1] (device, FP64).
 //
 // Precision: the exponent t_k = -log2(e) |x - c_k|^2 / (2 r_k^2) is taken in
 // FP64 (full rate on this chip, like float32 without packing): a softmax
@@ -254,29 +255,88 @@ __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint
 // (float32 inside a block, FP64 across blocks), and the higher coefficients
 // sum_k mean(w_k) h_k are formed in FP64 once per voxel.
 //
-// The records are read inside the sample loop through an offset the
-// compiler cannot prove constant (zero is 0), so they arrive by scalar
-// loads from cache each sample instead of being held across the loop, where
-// they would overflow the scalar register file; groups of four blobs are
-// separated by scheduling barriers so that the loads are not all issued at
-// once.  The Philox round keys are likewise recomputed by scalar adds.
+// The kernel is bound by VALU issue (about four cycles per wave instruction,
+// transcendentals sixteen), so what it does per sample is kept down:
+//  - CENTRED: the exponents are taken relative to their maximum at the voxel's
+//    centre, m, as a_k |x|^2 + b_k . x + (C_k - m): five FP64 instructions per
+//    blob instead of nine (differences, square, scale, maximum over the blobs,
+//    difference to it).  The host takes this form when no exponent changes by
+//    more than 64 within half a voxel diagonal, so that exp2 neither overflows
+//    nor loses a sample's largest term (the bound keeps the terms themselves,
+//    which cancel in FP64, below 1e5 at depth 10); m is rounded to a whole
+//    number, so 2^m is exact.  Otherwise the maximum is
+//    each sample's own.
+//  - Philox: of counter (code, j, 0, 0), round 1's products and one of round
+//    2's depend on the voxel or on j alone: the former are taken once per
+//    voxel, the latter are scalar.
+//  - Only the shells that a voxel of the wave can touch are tested.
+//  - PRODUCT: the logarithms of up to four samples' DC terms are taken of
+//    their product (three roundings of 2^-24 instead of three logarithms'
+//    errors); the host takes this form when the products stay within range
+//    and no radiance is close to L_max.  Otherwise each term has its own
+//    logarithm, and L_max - E, which would cancel, is summed from the blobs'
+//    L_max - e_k.
+// 256^3, 882k voxels kept, 256 samples, 16 blobs, 4 shells: 1.99 ms (2.95 ms
+// with nine FP64 instructions per blob, all shells tested, a logarithm per
+// sample and the radiance sums sunk below the shell loop); VALU busy 97 %.
+// (Taking the exponents and the sums over the blobs to the matrix cores, a
+// wave per voxel, was slower, 3.16 ms: FP64 and float32 MFMA take the cycles
+// of the FMAs they replace, and no VALU work ran beside them.)
+//
+// rec: NB records of four doubles -- CENTRED: b_k and a_k, else the centre and
+// a_k = -log2(e) / (2 r_k^2) --, NB constant terms C_k, then NB float4 records
+// (amplitude, radiance) and NB of (0, L_max - radiance); those past nb are padded so that their terms vanish
+// (exp2 of a huge negative argument is exactly 0).  The records are read
+// inside the sample loop through an offset the compiler cannot prove constant
+// (zero is 0), so they arrive by scalar loads from cache each sample instead
+// of being held across the loop, where they would overflow the scalar
+// register file; groups of four blobs are separated by scheduling barriers so
+// that the loads are not all issued at once.
 constexpr int kBlock = 16;
+constexpr int kProduct = 4;   // DC terms per logarithm
 
-template <int NB>
-__global__ __launch_bounds__(kThreads) void k_distill(const FieldArgs f, const double *__restrict__ rec,
+template <int NB, bool CENTRED, bool PRODUCT>
+__global__ __launch_bounds__(kThreads, NB == 8 ? 5 : NB == 16 ? 4 : 2) void k_distill(const FieldArgs f, const double *__restrict__ rec,
                                                       uint32_t zero, const double *hi, int depth, int n_samples,
-                                                      uint32_t key0, uint32_t key1, const uint32_t *codes,
-                                                      uint64_t n, float *sigma_out, float *sh_out) {
-    const uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
+                                                      uint32_t key0, uint32_t key1,
+                                                      const uint32_t *codes, uint64_t n, float *sigma_out,
+                                                      float *sh_out) {
+    const uint64_t i0 = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+    const bool mine = i0 < n;
+    const uint64_t i = mine ? i0 : n - 1;    // lanes past the end repeat the last voxel
     const uint32_t code = codes[i];
     const double hd = 2.0 / (double)(1 << depth);
+    const double hd24 = hd * 0x1p-24;
     const double lox = -1.0 + (double)compact3(code) * hd;
     const double loy = -1.0 + (double)compact3(code >> 1) * hd;
     const double loz = -1.0 + (double)compact3(code >> 2) * hd;
     constexpr float kLog2e = 1.4426950408889634f;
     constexpr float kLn2InvY00 = 0.69314718055994531f * 3.5449077018110318f;
     const float log_base2 = f.log_base * kLog2e;
+    const double cx = lox + 0.5 * hd, cy = loy + 0.5 * hd, cz = loz + 0.5 * hd;
+    double m = -INFINITY;         // CENTRED: the largest exponent at the centre
+    if constexpr (CENTRED) {
+        const double c2 = fma(cz, cz, fma(cy, cy, cx * cx));
+        const double4 *qa = reinterpret_cast<const double4 *>(rec);
+        const double *qc = reinterpret_cast<const double *>(qa + NB);
+        for (int k = 0; k < f.nb; ++k) {
+            const double4 a = qa[k];
+            m = fmax(m, fma(a.x, cx, fma(a.y, cy, fma(a.z, cz, fma(a.w, c2, qc[k])))));
+        }
+        m = rint(m);              // 2^m exact
+    }
+    float scale = __builtin_amdgcn_exp2f((float)m) * kLog2e;
+    // shells that a voxel of this wave may touch: its centre within half a
+    // diagonal (and a margin) of the shell
+    uint32_t shells = 0;
+    for (int j = 0; j < f.ns; ++j) {
+        const double dx = cx - f.dsx[j], dy = cy - f.dsy[j], dz = cz - f.dsz[j];
+        const double dist = sqrt(dx * dx + dy * dy + dz * dz);
+        if (__any(fabs(dist - f.dsr[j]) < f.dhalf_width + 0.87 * hd + 1e-6)) shells |= 1u << j;
+    }
+    // Philox round 1 leaves (j ^ key0, 0, hi(p0) ^ key1, lo(p0))
+    const uint64_t p0 = (uint64_t)0xD2511F53u * code;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(p0 >> 32) ^ key1);
     double wsum[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) wsum[k] = 0.0;
@@ -287,61 +347,102 @@ __global__ __launch_bounds__(kThreads) void k_distill(const FieldArgs f, const d
 #pragma unroll
         for (int k = 0; k < NB; ++k) wb[k] = 0.0f;
         float sig_acc = 0.0f, dc0 = 0.0f, dc1 = 0.0f, dc2 = 0.0f;
+        float n0 = 1.0f, n1 = 1.0f, n2 = 1.0f, d0 = 1.0f, d1 = 1.0f, d2 = 1.0f;
         for (int j = j0; j < j1; ++j) {
             const uint32_t jz = (uint32_t)j & zero;   // 0, opaque to the compiler
             const double4 *qa = reinterpret_cast<const double4 *>(rec) + jz;
-            const float4 *qb = reinterpret_cast<const float4 *>(qa + NB);
+            const double *qc = reinterpret_cast<const double *>(qa + NB);
+            const float4 *qb = reinterpret_cast<const float4 *>(qc + NB);
             uint32_t u[4];
-            philox4x32_10(code, (uint32_t)j, 0u, 0u, key0 + jz, key1 + jz, u);
-            // the position exactly in FP64 (cell + offset: 34 bits)
-            const double x = lox + (double)(u[0] >> 8) * 0x1p-24 * hd;
-            const double y = loy + (double)(u[1] >> 8) * 0x1p-24 * hd;
-            const double z = loz + (double)(u[2] >> 8) * 0x1p-24 * hd;
-            // t_k = log2 of blob k's Gaussian, m = max_k t_k (FP64)
-            double t[NB];
-            double m = -INFINITY;
-#pragma unroll
-            for (int g = 0; g < NB; g += 4) {
-#pragma unroll
-                for (int k = g; k < g + 4; ++k) {
-                    const double4 a = qa[k];
-                    const double dx = x - a.x, dy = y - a.y, dz = z - a.z;
-                    t[k] = fma(dz, dz, fma(dy, dy, dx * dx)) * a.w;
-                    m = fmax(m, t[k]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+            {
+                const uint32_t k0 = key0 + jz, k1 = key1 + jz;
+                const uint64_t q0 = (uint64_t)0xD2511F53u * ((uint32_t)j ^ k0);   // scalar
+                philox4x32_rounds<8>((uint32_t)(p1 >> 32) ^ (k0 + 0x9E3779B9u), (uint32_t)p1,
+                                     (uint32_t)(q0 >> 32) ^ (uint32_t)p0 ^ (k1 + 0xBB67AE85u), (uint32_t)q0,
+                                     k0 + 2u * 0x9E3779B9u, k1 + 2u * 0xBB67AE85u, u);
             }
+            // the position exactly in FP64 (cell + offset: 34 bits)
+            const double x = fma((double)(u[0] >> 8), hd24, lox);
+            const double y = fma((double)(u[1] >> 8), hd24, loy);
+            const double z = fma((double)(u[2] >> 8), hd24, loz);
+            // t_k = log2 of blob k's Gaussian, relative to m
+            double t[CENTRED ? 4 : NB];
+            if constexpr (!CENTRED) {
+                m = -INFINITY;
+#pragma unroll
+                for (int g = 0; g < NB; g += 4) {
+#pragma unroll
+                    for (int k = g; k < g + 4; ++k) {
+                        const double4 a = qa[k];
+                        const double dx = x - a.x, dy = y - a.y, dz = z - a.z;
+                        t[k] = fma(dz, dz, fma(dy, dy, dx * dx)) * a.w;
+                        m = fmax(m, t[k]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                scale = __builtin_amdgcn_exp2f((float)m) * kLog2e;
+            }
+            const double x2 = fma(z, z, fma(y, y, x * x));
             float e[NB];
             float s = 0.0f, sa = 0.0f, e0 = 0.0f, e1 = 0.0f, e2 = 0.0f;
+            float r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;   // L_max - E, of !PRODUCT
 #pragma unroll
             for (int g = 0; g < NB; g += 4) {
 #pragma unroll
                 for (int k = g; k < g + 4; ++k) {
                     const float4 b = qb[k];
-                    e[k] = __builtin_amdgcn_exp2f((float)(t[k] - m));
+                    if constexpr (CENTRED) {
+                        const double4 a = qa[k];
+                        const double tk = fma(a.x, x, fma(a.y, y, fma(a.z, z, fma(a.w, x2, qc[k] - m))));
+                        e[k] = __builtin_amdgcn_exp2f((float)tk);
+                    } else {
+                        e[k] = __builtin_amdgcn_exp2f((float)(t[k] - m));
+                    }
                     s += e[k];
                     sa = fmaf(b.x, e[k], sa);
                     e0 = fmaf(b.y, e[k], e0);
                     e1 = fmaf(b.z, e[k], e1);
                     e2 = fmaf(b.w, e[k], e2);
+                    if constexpr (!PRODUCT) {
+                        const float4 c = qb[NB + k];
+                        r0 = fmaf(c.y, e[k], r0);
+                        r1 = fmaf(c.z, e[k], r1);
+                        r2 = fmaf(c.w, e[k], r2);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            // the sums belong here: sunk below the shells, they would keep every
+            // blob's record in scalar registers until then
+            asm volatile("" : "+v"(s), "+v"(e0), "+v"(e1), "+v"(e2));
             const float inv = __builtin_amdgcn_rcpf(s);
 #pragma unroll
             for (int k = 0; k < NB; ++k) wb[k] = fmaf(e[k], inv, wb[k]);
             // density: exp(log_base + sum_k a_k g_k), sum_k a_k g_k = 2^m sa
-            float sg = fminf(
-                __builtin_amdgcn_exp2f(fmaf(__builtin_amdgcn_exp2f((float)m) * kLog2e, sa, log_base2)),
-                f.sigma_max);
-            if (f.ns > 0 && in_shell(f, x, y, z)) sg = f.sigma_max;
+            float sg = fminf(__builtin_amdgcn_exp2f(fmaf(scale, sa, log_base2)), f.sigma_max);
+            if (shells) {
+                const float xf = (float)x, yf = (float)y, zf = (float)z;
+                for (uint32_t rest = shells; rest; rest &= rest - 1)
+                    if (in_one_shell(f, __builtin_ctz(rest), xf, yf, zf, x, y, z)) sg = f.sigma_max;
+            }
             sig_acc += sg;
             // DC: logit(E / L_max) / Y_00 = ln(E / (L_max - E)) 2 sqrt(pi),
-            // E = e_c / s: log2(e_c / (L_max s - e_c)) ln 2 2 sqrt(pi)
-            const float ls = f.l_max * s;
-            dc0 = fmaf(__builtin_amdgcn_logf(e0 * __builtin_amdgcn_rcpf(ls - e0)), kLn2InvY00, dc0);
-            dc1 = fmaf(__builtin_amdgcn_logf(e1 * __builtin_amdgcn_rcpf(ls - e1)), kLn2InvY00, dc1);
-            dc2 = fmaf(__builtin_amdgcn_logf(e2 * __builtin_amdgcn_rcpf(ls - e2)), kLn2InvY00, dc2);
+            // E = e_c / s
+            if constexpr (PRODUCT) {
+                const float E0 = e0 * inv, E1 = e1 * inv, E2 = e2 * inv;
+                n0 *= E0, n1 *= E1, n2 *= E2;
+                d0 *= f.l_max - E0, d1 *= f.l_max - E1, d2 *= f.l_max - E2;
+                if ((j & (kProduct - 1)) == kProduct - 1 || j + 1 == j1) {
+                    dc0 = fmaf(__builtin_amdgcn_logf(n0 * __builtin_amdgcn_rcpf(d0)), kLn2InvY00, dc0);
+                    dc1 = fmaf(__builtin_amdgcn_logf(n1 * __builtin_amdgcn_rcpf(d1)), kLn2InvY00, dc1);
+                    dc2 = fmaf(__builtin_amdgcn_logf(n2 * __builtin_amdgcn_rcpf(d2)), kLn2InvY00, dc2);
+                    n0 = n1 = n2 = d0 = d1 = d2 = 1.0f;
+                }
+            } else {
+                dc0 = fmaf(__builtin_amdgcn_logf(e0 * __builtin_amdgcn_rcpf(r0)), kLn2InvY00, dc0);
+                dc1 = fmaf(__builtin_amdgcn_logf(e1 * __builtin_amdgcn_rcpf(r1)), kLn2InvY00, dc1);
+                dc2 = fmaf(__builtin_amdgcn_logf(e2 * __builtin_amdgcn_rcpf(r2)), kLn2InvY00, dc2);
+            }
         }
 #pragma unroll
         for (int k = 0; k < NB; ++k) wsum[k] += (double)wb[k];
@@ -350,6 +451,7 @@ __global__ __launch_bounds__(kThreads) void k_distill(const FieldArgs f, const d
         dc1_sum += (double)dc1;
         dc2_sum += (double)dc2;
     }
+    if (!mine) return;
     const double invn = 1.0 / (double)n_samples;
     sigma_out[i] = (float)(sig_sum * invn);
     const int K = f.K;
@@ -644,22 +746,54 @@ lq_status field_args(const lq_field_desc *fd, int depth, float prune_sigma, Fiel
 }
 
 
-// The sample loop's blob records (k_distill), as bytes: NB x {cx, cy, cz,
-// -log2(e) / (2 r^2)} in FP64, then NB x {amplitude, radiance} in float32;
-// the records past nb sit far outside the field with a huge falloff, so
-// their exp2 terms are exactly 0, and their amplitude and radiance are 0.
-std::vector<unsigned char> blob_records(const FieldArgs &f, int NB) {
-    std::vector<unsigned char> r((size_t)NB * 48, 0);
+// Largest change of a blob's exponent t = -log2(e) |x - c|^2 / (2 r^2) from a
+// voxel's centre to any point of it, over the whole box.
+double exponent_change(const FieldArgs &f, int depth) {
+    const double half = 0.8660254037844387 * 2.0 / (double)(1 << depth);   // half a voxel's diagonal
+    double worst = 0.0;
+    for (int k = 0; k < f.nb; ++k) {
+        // farthest point of the box from the blob's centre
+        const double x = 1.0 + std::fabs(f.dcx[k]), y = 1.0 + std::fabs(f.dcy[k]), z = 1.0 + std::fabs(f.dcz[k]);
+        const double far = std::sqrt(x * x + y * y + z * z);
+        worst = std::max(worst, 1.4426950408889634 * f.dinv2r2[k] * half * (2.0 * far + half));
+    }
+    return worst;
+}
+
+// Whether products of four factors E and of four factors L_max - E stay within
+// 2^-100 .. 2^100; E, a mean of the blobs' radiances, lies between them.
+bool dc_products_in_range(const FieldArgs &f) {
+    float lo = f.l_max, hi = 0.0f;
+    for (int k = 0; k < f.nb; ++k) {
+        lo = std::min({lo, f.er[k], f.eg[k], f.eb[k]});
+        hi = std::max({hi, f.er[k], f.eg[k], f.eb[k]});
+    }
+    return lo > 0x1p-24f && f.l_max < 0x1p24f && f.l_max - hi > std::max(0x1p-24f, 0x1p-12f * f.l_max);
+}
+
+// The sample loop's blob records (layout at k_distill), as bytes.  Those past
+// nb: far outside the field with a huge falloff, or a constant term alone, so
+// that their exp2 terms are exactly 0; their amplitude and radiance are 0.
+std::vector<unsigned char> blob_records(const lq_field_desc *fd, const FieldArgs &f, int NB,
+                                        bool centred) {
+    std::vector<unsigned char> r((size_t)NB * 72, 0);
     for (int k = 0; k < NB; ++k) {
-        double q[4] = {1000.0, 1000.0, 1000.0, -1e300};
-        float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        double q[4] = {1000.0, 1000.0, 1000.0, -1e300}, c = -1e300;
+        float w[4] = {0.0f, 0.0f, 0.0f, 0.0f}, v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (centred) q[0] = q[1] = q[2] = q[3] = 0.0;
         if (k < f.nb) {
-            q[0] = f.dcx[k], q[1] = f.dcy[k], q[2] = f.dcz[k];
-            q[3] = -f.dinv2r2[k] * 1.4426950408889634;
+            const double a = -f.dinv2r2[k] * 1.4426950408889634;
+            const double s = centred ? -2.0 * a : 1.0;
+            q[0] = s * f.dcx[k], q[1] = s * f.dcy[k], q[2] = s * f.dcz[k];
+            q[3] = a;
+            c = a * (f.dcx[k] * f.dcx[k] + f.dcy[k] * f.dcy[k] + f.dcz[k] * f.dcz[k]);
             w[0] = f.amp[k], w[1] = f.er[k], w[2] = f.eg[k], w[3] = f.eb[k];
+            for (int c = 0; c < 3; ++c) v[1 + c] = (float)(fd->l_max - fd->blobs[8 * k + 5 + c]);
         }
         memcpy(r.data() + 32 * k, q, 32);
-        memcpy(r.data() + 32 * NB + 16 * k, w, 16);
+        memcpy(r.data() + 32 * NB + 8 * k, &c, 8);
+        memcpy(r.data() + 40 * NB + 16 * k, w, 16);
+        memcpy(r.data() + 56 * NB + 16 * k, v, 16);
     }
     return r;
 }
@@ -721,21 +855,27 @@ lq_status lq_distill_leaves(const lq_field_desc *field, int32_t max_depth, float
                        codes, (uint64_t)capacity);
     const unsigned nb = (unsigned)((total + kThreads - 1) / kThreads);
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    const bool product = dc_products_in_range(f);
+    const bool centred = product && exponent_change(f, max_depth) <= 64.0;
     const int NB = f.nb <= 8 ? 8 : f.nb <= 16 ? 16 : 32;
-    std::vector<unsigned char> rec = blob_records(f, NB);
+    std::vector<unsigned char> rec = blob_records(field, f, NB, centred);
     double *d_rec;
     if ((e = b.alloc(&d_rec, rec.size() / 8)) != hipSuccess) return dfail(LQ_ERR_OOM, "device copy of the blobs");
     if ((e = hipMemcpy(d_rec, rec.data(), rec.size(), hipMemcpyHostToDevice)) != hipSuccess)
         return dhip(e, "copying the blobs");
-    if (NB == 8)
-        hipLaunchKernelGGL(k_distill<8>, dim3(nb), dim3(kThreads), 0, s, f, d_rec, 0u, d_hi, max_depth, n_samples,
-                           k0, k1, codes, (uint64_t)total, sigma, sh);
-    else if (NB == 16)
-        hipLaunchKernelGGL(k_distill<16>, dim3(nb), dim3(kThreads), 0, s, f, d_rec, 0u, d_hi, max_depth, n_samples,
-                           k0, k1, codes, (uint64_t)total, sigma, sh);
-    else
-        hipLaunchKernelGGL(k_distill<32>, dim3(nb), dim3(kThreads), 0, s, f, d_rec, 0u, d_hi, max_depth, n_samples,
-                           k0, k1, codes, (uint64_t)total, sigma, sh);
+    const auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kThreads), 0, s, f, d_rec, 0u, d_hi, max_depth, n_samples, k0, k1,
+                           codes, (uint64_t)total, sigma, sh);
+    };
+    const auto form = [&](auto nb_tag) {
+        constexpr int N = decltype(nb_tag)::value;
+        if (centred) launch(k_distill<N, true, true>);
+        else if (product) launch(k_distill<N, false, true>);
+        else launch(k_distill<N, false, false>);
+    };
+    if (NB == 8) form(std::integral_constant<int, 8>());
+    else if (NB == 16) form(std::integral_constant<int, 16>());
+    else form(std::integral_constant<int, 32>());
     if ((e = hipGetLastError()) != hipSuccess) return dhip(e, "launching the distillation");
     // the scratch above is freed on return: wait for its last use
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return dhip(e, "the distillation");
