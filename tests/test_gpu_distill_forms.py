@@ -60,3 +60,22 @@ def test_forms_match_oracle(lq, radius, n_blobs, n_shells, samples, emission):
     es = np.abs(sig.cpu().numpy() - o_sig) / np.maximum(np.abs(o_sig), 1e-3)
     eh = np.abs(sh.cpu().numpy() - o_sh) / np.maximum(np.abs(o_sh), 1e-2)
     assert es.max() <= RTOL and eh.max() <= RTOL, (es.max(), eh.max())
+
+
+@pytest.mark.parametrize("depth,n_blobs,n_shells,radius", [(1, 2, 0, 0.5), (2, 5, 1, 0.5), (6, 16, 0, 0.3), (6, 9, 8, 0.05),
+                                                           (7, 32, 2, 0.15)])
+def test_kept_voxels_match_oracle(lq, depth, n_blobs, n_shells, radius):
+    """The kept voxels are a decision: words of 64 centres decided at once by
+    bounds, with amplitudes of both signs, agree with the oracle's centres
+    (other than those it names ambiguous)."""
+    p = field_params(inputs.TreeSpec(depth=depth, n_blobs=n_blobs, n_shells=n_shells, sh_degree=0, seed=60 + depth,
+                                     occupancy=0.3))
+    rng = np.random.default_rng(n_blobs)
+    p["radii"] = rng.uniform(1.0, 2.0, n_blobs) * radius
+    p["amps"] = np.array(p["amps"]) * np.where(np.arange(n_blobs) % 3 == 1, -1.0, 1.0)
+    print(f"[gpu] kept voxels, depth {depth}, {n_blobs} blobs, {n_shells} shells", flush=True)
+    codes, _, _ = lq.distill_leaves(p, depth, 0.01, 1, 5)
+    g_codes = codes.cpu().numpy().view(np.uint32).astype(np.uint64)
+    o_codes, amb = od.centre_occupancy(od.field_from_params(p), depth)
+    assert g_codes.size > 0 and np.all(np.diff(g_codes.astype(np.int64)) > 0)
+    assert np.all(np.isin(np.setxor1d(g_codes, o_codes), amb))
