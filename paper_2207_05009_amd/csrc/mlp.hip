@@ -11,11 +11,11 @@
 //   backward data GEMMs (MFMA 16x16x32 bf16, weights as the A operand, so one
 //   layer's output registers are the next layer's B operand), with the loss
 //   of Eq. 8 in between.  Features, activations and output gradients are also
-//   written to LDS, one row per feature, and after a barrier the 84 16x16
+//   written to LDS, one row per sample, and after a barrier the 84 16x16
 //   blocks of the weight gradients (K = the tile's 64 samples) are split over
-//   the 4 waves and accumulate in registers across the workgroup's tiles;
-//   bias gradients are row sums.  Each workgroup writes one partial gradient
-//   row.
+//   the 4 waves, take their operands by transposing LDS reads and accumulate
+//   in registers across the workgroup's tiles; bias gradients are products
+//   with ones.  Each workgroup writes one partial gradient row.
 //   k_reduce_adam: sums the rows in a fixed order (deterministic), applies
 //   Adam to the float32 master weights and scatters them to the bfloat16
 //   lane-ordered copy the kernels stage.
@@ -137,24 +137,44 @@ __device__ inline void sincos_run5(float x, float *f) {
 // for the backward, the transposed weights -- staged in LDS in lane order;
 // the ReLU masks come from the activations the lane still holds).  Every
 // GEMM input of the weight gradients (features, activations H_l, output
-// gradients dZ_l, dY) is also written to LDS feature-major, one row of 64
-// samples per feature.  Phase B, per workgroup: the weight gradients
-// dW_l = dZ_l H_{l-1}^T contract over the tile's 64 samples, so each MFMA
-// operand is 8 consecutive samples of one row (one ds_read_b128); their 84
-// 16x16 blocks are split over the 4 waves and accumulate in registers across
-// the workgroup's tiles; bias gradients are row sums.
-constexpr int kRS = 72;                              // LDS row stride (bf16): 64 samples + 8
-constexpr int kRowX = 0, kRowH = kRowX + kFeat;      // X: 128 rows, H1..H4: 64 rows each
-constexpr int kRowDZ = kRowH + 4 * kHidden;          // dZ1..dZ4: 64 rows each
-constexpr int kRowDY = kRowDZ + 4 * kHidden;         // dY: 4 rows (outputs 0..2, row 3 zero)
-constexpr int kRows = kRowDY + 4;
+// gradients dZ_l, dY) is also written to LDS, one row per sample: a lane
+// holds eight features of one sample, so that is one 16-byte store per eight
+// values.  Phase B, per workgroup: the weight gradients dW_l = dZ_l H_{l-1}^T
+// contract over the tile's 64 samples, so an MFMA operand is eight samples
+// of one feature; the transposing LDS read (ds_read_b64_tr_b16: 16 lanes
+// read 4 samples x 16 features, lane i receives feature i of the four) turns
+// the rows into it.  Wave w takes the output positions 16 w .. 16 w + 15 of
+// every layer, so each of its dZ operands serves all input blocks; 21 16x16
+// blocks, and the bias gradients as products with ones, accumulate in
+// registers across the workgroup's tiles.
+//
+// Bound by LDS throughput (weights, rows and operands through one LDS per
+// CU) with one wave per SIMD.  65536 samples (4 tiles per workgroup): 30 us;
+// 47 us with one row per feature (a 2-byte store per value, 16-byte operand
+// reads off a stride of 36 words, bias gradients as sums over rows).
+//
+// Columns of a row.  The features of X stand in slot order, those of H_l and
+// dZ_l in the order the lanes hold them (position_feature), dY takes 16
+// columns of which 3 are used.  The row stride is 8 mod 64 words, so that the
+// eight rows that half a wave reads at a time fall on different banks.
+constexpr int kColX = 0, kColH = kColX + kFeat;      // X: 128, H1..H4: 64 each
+constexpr int kColDZ = kColH + 4 * kHidden;          // dZ1..dZ4: 64 each
+constexpr int kColDY = kColDZ + 4 * kHidden;         // dY: 16 (outputs 0..2, then zeros)
+constexpr int kRow = kColDY + kOutPad;               // bf16 elements
+static_assert((kRow / 2) % 64 == 8 && kRow % 8 == 0, "bank layout and alignment of the sample rows");
+
+// feature (0..63) of column position p of an H_l or dZ_l
+__host__ __device__ constexpr int position_feature(int p) {
+    return 32 * (p >> 5) + 16 * ((p >> 2) & 1) + 4 * ((p >> 3) & 3) + (p & 3);
+}
+
 constexpr int kTW1 = 0;                              // bf16x8 [4 fb][4 kb][64]
 constexpr int kTWh = kTW1 + 16 * 64 * 16;            // bf16x8 [3 l][4 fb][2 kb][64] + output [2 kb][64]
 constexpr int kTWt = kTWh + 26 * 64 * 16;            // bf16x8 [3 l][4 ib][2 kb][64]: transposed W2..W4
 constexpr int kTW5t = kTWt + 24 * 64 * 16;           // bf16x4 [4 ib][64]: transposed W5 (K = 16)
 constexpr int kTB = kTW5t + 4 * 64 * 8;              // float [kBiasPad]
-constexpr int kTAct = kTB + kBiasPad * 4;            // bf16 [kRows][kRS]
-constexpr int kTLoss = kTAct + kRows * kRS * 2;      // float [kWaves]
+constexpr int kTAct = kTB + kBiasPad * 4;            // bf16 [kTile][kRow]
+constexpr int kTLoss = kTAct + kTile * kRow * 2;     // float [kWaves]
 constexpr int kTrainLds = kTLoss + kWaves * 4;
 static_assert(kTrainLds <= 160 * 1024, "training LDS carve exceeds the CU's LDS");
 
@@ -281,16 +301,50 @@ __device__ inline bf16x8 mask_pack(f32x4 lo, f32x4 hi, bf16x8 h) {
     return __builtin_bit_cast(bf16x8, pack8(lo, hi) & (zero - pos));
 }
 
-// write the h-layout pair hv (features 16 (2 kb + e / 4) + 4 g + e % 4 of
-// sample col) feature-major into the rows starting at row0
-__device__ inline void store_rows(uint16_t *act, int row0, const bf16x8 (&hv)[2], int g, int col) {
+// write the h-layout pair hv into the sample's row, from column c0
+__device__ inline void store_cols(uint16_t *row, int c0, const bf16x8 (&hv)[2], int g) {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        const s16x8 v = __builtin_bit_cast(s16x8, hv[kb]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            act[(row0 + (2 * kb + (e >> 2)) * 16 + 4 * g + (e & 3)) * kRS + col] = (uint16_t)v[e];
+    for (int kb = 0; kb < 2; ++kb) *reinterpret_cast<bf16x8 *>(row + c0 + 32 * kb + 8 * g) = hv[kb];
+}
+
+// A workgroup's partial gradients: the 84 blocks as the lanes hold them
+// ([wave][21][lane][4], so a lane stores 16 bytes at once), then the biases
+// ([layer][position], b5).  Blocks of a wave: 0..7 dW1, 8..19 dW2..dW4 (4
+// each), 20 dW5.
+constexpr int kPartBias = kWaves * 21 * 256;
+constexpr int kPartRow = kPartBias + 4 * kHidden + 4;
+static_assert(kPartRow % 4 == 0, "16-byte stores of a partial row");
+
+// parameter at element q of a partial row (-1: padding)
+__host__ __device__ constexpr int part_param(int q) {
+    if (q >= kPartBias) {
+        const int l = (q - kPartBias) >> 6, p = (q - kPartBias) & 63;
+        if (l == 4) return p < kOut ? kB5 + p : -1;
+        return (l == 0 ? kB1 : l == 1 ? kB2 : l == 2 ? kB3 : kB4) + position_feature(p);
     }
+    const int w = q / (21 * 256), slot = (q >> 8) % 21, lane = (q >> 2) & 63;
+    const int m = 4 * (lane >> 4) + (q & 3), n = lane & 15;   // row and column of the block
+    if (slot < 8) {
+        const int p = 16 * slot + n;                          // column of X: 32 kb + 8 g + e
+        return kW1 + position_feature(16 * w + m) * kFeat + slot_feature((p >> 3) & 3, (p >> 5) * 8 + (p & 7));
+    }
+    if (slot < 20) {
+        const int l = (slot - 8) >> 2;
+        return kW2 + l * (kW3 - kW2) + position_feature(16 * w + m) * kHidden + position_feature(16 * ((slot - 8) & 3) + n);
+    }
+    return m < kOut ? kW5 + m * kHidden + position_feature(16 * w + n) : -1;
+}
+
+// the K = 32 operand over samples 32 grp .. 32 grp + 31 for the 16 columns
+// from c0: lane 16 g + r receives column c0 + r of samples 4 g .. 4 g + 3 and
+// 16 + 4 g .. 16 + 4 g + 3 of the group.  rows: the tile's rows moved to the
+// element this lane reads first (sample 4 g + r / 4, column 4 (r % 4)).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+__device__ inline bf16x8 sample_operand(uint16_t *rows, int grp, int c0) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(rows + grp * 32 * kRow + c0));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(rows + (grp * 32 + 16) * kRow + c0));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 __global__ __launch_bounds__(256) void k_train_step(const float *o, const float *d, const float *tgt,
@@ -315,6 +369,9 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
         for (int k = 0; k < kTB / (16 * 256); ++k) dst[k * 256 + threadIdx.x] = src[k * 256 + threadIdx.x];
     }
     for (int i = threadIdx.x; i < kBiasPad; i += blockDim.x) sB[i] = bias[i];
+    // columns 4..15 of dY stay zero
+    for (int i = threadIdx.x; i < kTile * 3; i += blockDim.x)
+        *reinterpret_cast<uint2 *>(act + (i / 3) * kRow + kColDY + 4 + 4 * (i % 3)) = uint2{0u, 0u};
     __syncthreads();
 
     const int wave = threadIdx.x >> 6;
@@ -325,8 +382,15 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
     f32x4 gacc[21];
 #pragma unroll
     for (int j = 0; j < 21; ++j) gacc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float gbias = 0.0f, gb5 = 0.0f, lsum = 0.0f;
+    f32x4 gb[5];                         // bias gradients: the wave's positions of b1..b4, b5
+#pragma unroll
+    for (int j = 0; j < 5; ++j) gb[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float lsum = 0.0f;
     const bf16x8 zero8 = {};
+    const s16x8 one16 = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, one16);
+    uint16_t *row = act + col * kRow;                                // this lane's sample
+    uint16_t *rows = act + (4 * g + (r16 >> 2)) * kRow + 4 * (r16 & 3);   // of sample_operand
 
     // the pair of the lane's sample in tile t (false: past the batch)
     auto pair_of = [&](int t, int64_t &ray) {
@@ -390,9 +454,7 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
             const f32x4 lo = {f[kb * 8], f[kb * 8 + 1], f[kb * 8 + 2], f[kb * 8 + 3]};
             const f32x4 hi = {f[kb * 8 + 4], f[kb * 8 + 5], f[kb * 8 + 6], f[kb * 8 + 7]};
             x[kb] = actv ? __builtin_bit_cast(bf16x8, pack8(lo, hi)) : zero8;
-            const s16x8 v = __builtin_bit_cast(s16x8, x[kb]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) act[(kRowX + slot_feature(g, kb * 8 + e)) * kRS + col] = (uint16_t)v[e];
+            *reinterpret_cast<bf16x8 *>(row + kColX + 32 * kb + 8 * g) = x[kb];
         }
 
         // forward
@@ -406,7 +468,7 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
             for (int fb = 0; fb < 4; ++fb) acc[fb] = mfma32(sW1[(fb * 4 + kb) * 64 + lane], x[kb], acc[fb]);
         h[0][0] = relu_pack(acc[0], acc[1]);
         h[0][1] = relu_pack(acc[2], acc[3]);
-        store_rows(act, kRowH, h[0], g, col);
+        store_cols(row, kColH, h[0], g);
 #pragma unroll
         for (int l = 0; l < 3; ++l) {
 #pragma unroll
@@ -419,7 +481,7 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
                     acc[fb] = mfma32(sWh[((l * 4 + fb) * 2 + kb) * 64 + lane], h[l][kb], acc[fb]);
             h[l + 1][0] = relu_pack(acc[0], acc[1]);
             h[l + 1][1] = relu_pack(acc[2], acc[3]);
-            store_rows(act, kRowH + (l + 1) * kHidden, h[l + 1], g, col);
+            store_cols(row, kColH + (l + 1) * kHidden, h[l + 1], g);
         }
         f32x4 y = *reinterpret_cast<const f32x4 *>(sB + 4 * kHidden + 4 * g);
         y = mfma32(sWh[24 * 64 + lane], h[3][0], y);
@@ -447,10 +509,7 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
             lsum += lsmp;
         }
         const bf16x4b dyb = {(__bf16)gy[0], (__bf16)gy[1], (__bf16)gy[2], (__bf16)gy[3]};
-        if (g == 0) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) act[(kRowDY + c) * kRS + col] = f2bf(gy[c]);   // = dyb[c]
-        }
+        if (g == 0) *reinterpret_cast<bf16x4b *>(row + kColDY) = dyb;
 
         // backward data: dZ4 = (W5^T dY) masked by H4 > 0, then down to dZ1
         bf16x8 z[2];
@@ -458,7 +517,7 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
         for (int ib = 0; ib < 4; ++ib) acc[ib] = mfma16b(sW5t[ib * 64 + lane], dyb, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
         z[0] = mask_pack(acc[0], acc[1], h[3][0]);
         z[1] = mask_pack(acc[2], acc[3], h[3][1]);
-        store_rows(act, kRowDZ + 3 * kHidden, z, g, col);
+        store_cols(row, kColDZ + 3 * kHidden, z, g);
 #pragma unroll
         for (int l = 2; l >= 0; --l) {    // dZ_{l+1} from dZ_{l+2} through W_{l+2}
 #pragma unroll
@@ -470,90 +529,41 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
                     acc[ib] = mfma32(sWt[((l * 4 + ib) * 2 + kb) * 64 + lane], z[kb], acc[ib]);
             z[0] = mask_pack(acc[0], acc[1], h[l][0]);
             z[1] = mask_pack(acc[2], acc[3], h[l][1]);
-            store_rows(act, kRowDZ + l * kHidden, z, g, col);
+            store_cols(row, kColDZ + l * kHidden, z, g);
         }
         __syncthreads();
 
         // ---- phase B: weight-gradient blocks over the tile's 64 samples
 #pragma unroll
-        for (int slot = 0; slot < 21; ++slot) {
-            const int j = slot * kWaves + wave;   // block 0..83
-            int arow, brow;
-            bool arow_ok = true;
-            if (j < 32) {
-                arow = kRowDZ + (j >> 3) * 16;
-                brow = kRowX + (j & 7) * 16;
-            } else if (j < 80) {
-                const int l = 2 + (j - 32) / 16, jj = (j - 32) % 16;
-                arow = kRowDZ + (l - 1) * kHidden + (jj >> 2) * 16;
-                brow = kRowH + (l - 2) * kHidden + (jj & 3) * 16;
-            } else {
-                arow = kRowDY;
-                arow_ok = r16 < 4;                 // output rows 4..15 are padding
-                brow = kRowH + 3 * kHidden + (j - 80) * 16;
-            }
-            f32x4 a_acc = gacc[slot];
+        for (int grp = 0; grp < 2; ++grp) {
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const int c0 = kb * 32 + 8 * g;
-                const bf16x8 ar = *reinterpret_cast<const bf16x8 *>(act + (arow + (arow_ok ? r16 : 0)) * kRS + c0);
-                const bf16x8 av = arow_ok ? ar : zero8;
-                const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(act + (brow + r16) * kRS + c0);
-                a_acc = mfma32(av, bv, a_acc);
-            }
-            gacc[slot] = a_acc;
-        }
-        // bias gradients: thread t owns b_{t/64 + 1}[t % 64]; threads 0..2 b_5
-        {
-            const int t = threadIdx.x;
-            const uint16_t *rowp = act + (kRowDZ + t) * kRS;     // dZ rows of the four hidden layers
-            float sacc = 0.0f;
+            for (int l = 0; l < 4; ++l) {
+                const bf16x8 dz = sample_operand(rows + 16 * wave, grp, kColDZ + l * kHidden);
+                gb[l] = mfma32(dz, ones, gb[l]);
 #pragma unroll
-            for (int c = 0; c < kTile; c += 8) {
-                const s16x8 v = *reinterpret_cast<const s16x8 *>(rowp + c);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sacc += bf2f((uint16_t)v[e]);
-            }
-            gbias += sacc;
-            if (t < kOut) {
-                const uint16_t *r5 = act + (kRowDY + t) * kRS;
-                float s5 = 0.0f;
-#pragma unroll
-                for (int c = 0; c < kTile; c += 8) {
-                    const s16x8 v = *reinterpret_cast<const s16x8 *>(r5 + c);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) s5 += bf2f((uint16_t)v[e]);
+                for (int ib = 0; ib < (l == 0 ? 8 : 4); ++ib) {
+                    const int slot = l == 0 ? ib : 4 + 4 * l + ib;
+                    const int c0 = (l == 0 ? kColX : kColH + (l - 1) * kHidden) + 16 * ib;
+                    gacc[slot] = mfma32(dz, sample_operand(rows, grp, c0), gacc[slot]);
                 }
-                gb5 += s5;
             }
+            const bf16x8 dy = sample_operand(rows, grp, kColDY);
+            gb[4] = mfma32(dy, ones, gb[4]);
+            gacc[20] = mfma32(dy, sample_operand(rows + 16 * wave, grp, kColH + 3 * kHidden), gacc[20]);
         }
         __syncthreads();
     }
 
     // ---- write this workgroup's partial gradient row
-    float *P = part + (size_t)blockIdx.x * kParams;
+    float *P = part + (size_t)blockIdx.x * kPartRow;
 #pragma unroll
-    for (int slot = 0; slot < 21; ++slot) {
-        const int j = slot * kWaves + wave;
-        int woff, in_dim, out_dim, ob, ib;
-        if (j < 32) { woff = kW1; in_dim = kFeat; out_dim = kHidden; ob = j >> 3; ib = j & 7; }
-        else if (j < 80) {
-            const int l = 2 + (j - 32) / 16, jj = (j - 32) % 16;
-            woff = l == 2 ? kW2 : (l == 3 ? kW3 : kW4);
-            in_dim = kHidden; out_dim = kHidden; ob = jj >> 2; ib = jj & 3;
-        } else { woff = kW5; in_dim = kHidden; out_dim = kOut; ob = 0; ib = j - 80; }
+    for (int slot = 0; slot < 21; ++slot)
+        *reinterpret_cast<f32x4 *>(P + ((wave * 21 + slot) * 64 + lane) * 4) = gacc[slot];
+    if (r16 == 0) {                      // all columns of gb are alike
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int out = ob * 16 + 4 * g + i;
-            const int in = ib * 16 + r16;
-            if (out < out_dim) P[woff + out * in_dim + in] = gacc[slot][i];
-        }
-    }
-    {
-        const int t = threadIdx.x;
-        const int boff = t < 64 ? kB1 : (t < 128 ? kB2 : (t < 192 ? kB3 : kB4));
-        P[boff + (t & 63)] = gbias;
-        if (t < kOut) P[kB5 + t] = gb5;
+        for (int l = 0; l < 4; ++l)
+            *reinterpret_cast<f32x4 *>(P + kPartBias + l * kHidden + 16 * wave + 4 * g) = gb[l];
+        if (wave == 0 && g == 0) *reinterpret_cast<f32x4 *>(P + kPartBias + 4 * kHidden) = gb[4];
     }
     // loss partial: lanes 0..15 of each wave hold per-sample sums
     float l = lsum;
@@ -578,7 +588,7 @@ __device__ inline int bias_index(int p) {
 }
 
 // Sum of the partial gradient rows and the Adam update.  A block takes
-// kRedParams consecutive parameters; its kRedWaves waves sum fixed slices of
+// kRedParams consecutive elements of a row; its kRedWaves waves sum fixed slices of
 // the rows with all of a slice's loads in flight, and wave 0 adds the slices
 // in a fixed order: the result does not depend on scheduling, so a resumed
 // run repeats an uninterrupted one bit for bit.  Block 0 also sums the
@@ -595,14 +605,14 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_adam(const float *par
     __shared__ float s_part[kRedWaves][kRedParams];
     __shared__ float s_loss[256];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int p = blockIdx.x * kRedParams + lane;
+    const int q = blockIdx.x * kRedParams + lane;
     float g = 0.0f;
-    if (p < kParams) {
+    if (q < kPartRow) {
         const int r0 = rows * w / kRedWaves, r1 = rows * (w + 1) / kRedWaves;
         for (int r = r0; r < r1; r += kRedRows) {
             float a[kRedRows];
 #pragma unroll
-            for (int j = 0; j < kRedRows; ++j) a[j] = r + j < r1 ? part[(size_t)(r + j) * kParams + p] : 0.0f;
+            for (int j = 0; j < kRedRows; ++j) a[j] = r + j < r1 ? part[(size_t)(r + j) * kPartRow + q] : 0.0f;
 #pragma unroll
             for (int st = kRedRows / 2; st > 0; st >>= 1)
 #pragma unroll
@@ -624,7 +634,9 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_adam(const float *par
         }
         if (threadIdx.x == 0) *loss_out = s_loss[0];
     }
-    if (w != 0 || p >= kParams) return;
+    if (w != 0 || q >= kPartRow) return;
+    const int p = part_param(q);
+    if (p < 0) return;
     float sl[kRedWaves];
 #pragma unroll
     for (int j = 0; j < kRedWaves; ++j) sl[j] = s_part[j][lane];
@@ -999,7 +1011,7 @@ static lq_status alloc_mlp(int device, lq_mlp **out) {
               hipMalloc((void **)&p->v, kParams * 4) == hipSuccess &&
               hipMalloc((void **)&p->wlane, kLaneElems * 2) == hipSuccess &&
               hipMalloc((void **)&p->bias, kBiasPad * 4) == hipSuccess &&
-              hipMalloc((void **)&p->part, (size_t)p->part_rows * kParams * 4) == hipSuccess &&
+              hipMalloc((void **)&p->part, (size_t)p->part_rows * kPartRow * 4) == hipSuccess &&
               hipMalloc((void **)&p->loss_part, (size_t)p->part_rows * 4) == hipSuccess &&
               hipMalloc((void **)&p->trust, kTrustBins) == hipSuccess;
     if (!ok) {
@@ -1130,7 +1142,8 @@ lq_status lq_mlp_grad(lq_mlp *p, const float *o, const float *d, const float *rg
     int rows = 0;
     e = launch_step(p, o, d, rgb, n, 0, n, rows, s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_reduce_adam, dim3((kParams + kRedParams - 1) / kRedParams), dim3(64 * kRedWaves), 0, s, p->part, rows, p->theta,
+        hipLaunchKernelGGL(k_reduce_adam, dim3((kPartRow + kRedParams - 1) / kRedParams), dim3(64 * kRedWaves), 0, s, p->part,
+                           rows, p->theta,
                            p->m, p->v, p->wlane, p->bias, p->loss_part, loss_dev, grad, 0, 0.0f, 0.0f, 0.0f, 0.0f,
                            0.0f, 0.0f);
         e = hipGetLastError();
@@ -1175,7 +1188,8 @@ lq_status lq_mlp_train(lq_mlp *p, const float *o, const float *d, const float *r
         const double t = (double)(gstep + 1);
         const float c1 = (float)(1.0 / (1.0 - pow((double)cfg->beta1, t)));
         const float c2 = (float)(1.0 / (1.0 - pow((double)cfg->beta2, t)));
-        hipLaunchKernelGGL(k_reduce_adam, dim3((kParams + kRedParams - 1) / kRedParams), dim3(64 * kRedWaves), 0, s, p->part, rows, p->theta,
+        hipLaunchKernelGGL(k_reduce_adam, dim3((kPartRow + kRedParams - 1) / kRedParams), dim3(64 * kRedWaves), 0, s, p->part,
+                           rows, p->theta,
                            p->m, p->v, p->wlane, p->bias, p->loss_part, loss_dev + k, (float *)nullptr, 1, lr,
                            cfg->beta1, cfg->beta2, cfg->eps, c1, c2);
         e = hipGetLastError();
