@@ -16,8 +16,7 @@
 // live ones (weight > 0) with their rays, the persistent emission query
 // marches the listed rays only, k_proxy_reduce blends and sums per point in
 // sample order (FP64 sums).  Listing first matters: rays that need no march
-// interleaved with live ones would make the query's refills draw again and
-// again from its shared ray counters.
+// would take lanes of the query's waves for nothing.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -87,88 +86,111 @@ __device__ inline int face_direction_bin(int a, double w0, double w1, double w2,
 
 constexpr double kFaceMix = 0.5;   // share of the face choice weighted by the face-centre geometry
 
-// Picks the cell of a guided sample.  The point x (normal n) sees the faces
-// with side * x_axis > 1.  On face f it uses table b_f, the direction bin
-// of x - c_f (c_f the face's centre); P_f = cdf_b_f[(f + 1) G^2] -
-// cdf_b_f[f G^2] is the face's guide mass, P_vis their sum,
+// The faces a guided point may sample.  The point x (normal n) sees the faces
+// with side * x_axis > 1: at most one per axis.  On face f it uses table b_f,
+// the direction bin of x - c_f (c_f the face's centre); P_f = cdf_b_f[(f + 1)
+// G^2] - cdf_b_f[f G^2] is the face's guide mass, P_vis their sum,
 // g_f = max(0, n.(c_f - x)) (side x_axis - 1) / |c_f - x|^4 the irradiance
 // integrand cos cos / r^2 at the face centre (up to the constant 1/|n|)
 // and S the sum of P_f g_f.  Face f is taken with probability
 // Q_f = kFaceMix P_f g_f / S + (1 - kFaceMix) P_f / P_vis (P_f / P_vis when
-// S = 0), the cell within it by inverting its table.  All of it in FP64
-// from the float32 inputs, sums in axis and face order, so that the choice
-// is reproducible bit for bit.  Returns the cell (-1 when no face is visible
-// or P_vis = 0), its table in `bin` and Q_f / P_f in `factor`: the
-// sample's area density is prob_bin[k] factor / A_cell.
+// S = 0), the cell within it by inverting its table: the sample's area
+// density is prob_bin[k] (Q_f / P_f) / A_cell.  All of it in FP64 from the
+// float32 inputs, sums in axis and face order, so that the choice is
+// reproducible bit for bit.
+struct Faces {           // per axis
+    int face[3];         // 8 b_f + f of the face seen, or -1 (all -1 when P_vis = 0)
+    double P[3], Q[3];
+    double factor[3];    // Q / P, 0 when P = 0
+    double c0[3];        // cdf_b_f[f G^2]
+};
+
 template <bool DIR>
-__device__ inline int guide_cell(const Guide &g, float x0, float x1, float x2, float n0, float n1, float n2,
-                                 float u0, int &bin, double &factor) {
+__device__ inline Faces guide_faces(const Guide &g, float x0, float x1, float x2, float n0, float n1, float n2) {
     const int gg = g.G * g.G;
     const int stride = g.n_cells + 1;
     const double xd[3] = {(double)x0, (double)x1, (double)x2};
     const double nd[3] = {(double)n0, (double)n1, (double)n2};
-    bool vis[6];
-    int fb[6];
-    double P[6], Q[6], gf[6];
+    Faces F;
+    double gf[3];
     double pv = 0.0, gs = 0.0;
-    int last = -1;
-    factor = 0.0;
-    bin = 0;
 #pragma unroll
-    for (int f = 0; f < 6; ++f) {
-        const int ax = f >> 1;
+    for (int ax = 0; ax < 3; ++ax) {
         const float xa = ax == 0 ? x0 : (ax == 1 ? x1 : x2);
-        vis[f] = ((f & 1) ? xa : -xa) > 1.0f;
-        P[f] = 0.0;
-        gf[f] = 0.0;
-        fb[f] = 0;
-        if (vis[f]) {
+        F.face[ax] = -1;
+        F.P[ax] = F.Q[ax] = F.factor[ax] = F.c0[ax] = gf[ax] = 0.0;
+        if (fabsf(xa) > 1.0f) {
+            const int f = 2 * ax + (xa > 0.0f ? 1 : 0);
             const double sg = (f & 1) ? 1.0 : -1.0;
             double d[3];
 #pragma unroll
             for (int b = 0; b < 3; ++b) d[b] = (b == ax ? sg : 0.0) - xd[b];
             // the outward direction x - c_f is -d
-            if constexpr (DIR) fb[f] = face_direction_bin(ax, -d[0], -d[1], -d[2], g.D);
-            const double *c = g.cdf + (size_t)fb[f] * stride;
-            P[f] = c[(f + 1) * gg] - c[f * gg];
+            int fb = 0;
+            if constexpr (DIR) fb = face_direction_bin(ax, -d[0], -d[1], -d[2], g.D);
+            F.face[ax] = 8 * fb + f;
+            const double *c = g.cdf + (size_t)fb * stride;
+            F.c0[ax] = c[f * gg];
+            F.P[ax] = c[(f + 1) * gg] - c[f * gg];
             const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
             const double ndot = nd[0] * d[0] + nd[1] * d[1] + nd[2] * d[2];
             const double h = sg * xd[ax] - 1.0;
-            gf[f] = ndot > 0.0 ? (ndot * h) / (r2 * r2) : 0.0;
-            pv += P[f];
-            gs += P[f] * gf[f];
-            last = f;
+            gf[ax] = ndot > 0.0 ? (ndot * h) / (r2 * r2) : 0.0;
+            pv += F.P[ax];
+            gs += F.P[ax] * gf[ax];
         }
     }
-    if (!(pv > 0.0)) return -1;
 #pragma unroll
-    for (int f = 0; f < 6; ++f)
-        Q[f] = !vis[f] ? 0.0
-                       : (gs > 0.0 ? kFaceMix * (P[f] * gf[f] / gs) + (1.0 - kFaceMix) * (P[f] / pv) : P[f] / pv);
-    double t = (double)u0;
-    for (int f = 0; f < 6; ++f) {
-        if (!vis[f]) continue;
-        if (t < Q[f] || f == last) {
-            const double *c = g.cdf + (size_t)fb[f] * stride;
-            const double r = Q[f] > 0.0 ? t / Q[f] : 0.0;
-            const double target = c[f * gg] + r * P[f];
-            int lo = f * gg, hi = f * gg + gg - 1;   // c[lo] <= target holds for lo = f gg
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (c[mid] <= target) lo = mid;
-                else hi = mid - 1;
-            }
-            factor = P[f] > 0.0 ? Q[f] / P[f] : 0.0;
-            bin = fb[f];
-            return lo;
-        }
-        t -= Q[f];
+    for (int ax = 0; ax < 3; ++ax) {
+        if (!(pv > 0.0)) F.face[ax] = -1;
+        if (F.face[ax] < 0) continue;
+        F.Q[ax] = gs > 0.0 ? kFaceMix * (F.P[ax] * gf[ax] / gs) + (1.0 - kFaceMix) * (F.P[ax] / pv) : F.P[ax] / pv;
+        F.factor[ax] = F.P[ax] > 0.0 ? F.Q[ax] / F.P[ax] : 0.0;
     }
-    return -1;
+    return F;
+}
+
+// The axis whose face the number u0 picks (the last one seen when u0 lies
+// past the sum); t: what is left of u0 there.  -1: no face.
+__device__ inline int pick_face(const int (&face)[3], const double (&Q)[3], float u0, double &t) {
+    const int last = face[2] >= 0 ? 2 : (face[1] >= 0 ? 1 : (face[0] >= 0 ? 0 : -1));
+    t = (double)u0;
+    int pick = -1;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        if (pick >= 0 || face[ax] < 0) continue;
+        if (t < Q[ax] || ax == last) pick = ax;
+        else t -= Q[ax];
+    }
+    return pick;
+}
+
+// The cell in the face (8 b_f + f) by inverting its table.
+__device__ inline int guide_cell(const Guide &g, int face, double P, double Q, double c0, double t) {
+    const int gg = g.G * g.G, f = face & 7;
+    const double *c = g.cdf + (size_t)(face >> 3) * (g.n_cells + 1);
+    const double r = Q > 0.0 ? t / Q : 0.0;
+    const double target = c0 + r * P;
+    int lo = f * gg, hi = f * gg + gg - 1;   // c[lo] <= target holds for lo = f gg
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (c[mid] <= target) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
 }
 
 // DIR: a direction-binned guide (D > 1); the direction-averaged and the
 // uniform samplers are compiled without the bin decisions.
+//
+// A point's faces (three direction bins in FP64 with their thresholds, six
+// FP64 divisions) are the same for all its samples: where a block's samples
+// belong to at most kTablePoints points (8 samples per point and more), the
+// block forms them once per point in LDS; with fewer samples per point each
+// sample forms its own.  262144 points x 16 samples, 16^2 cells, 2 x 2 bins:
+// 104 us, 144 us when every sample did (the bytes moved take about 40).
+constexpr int kTablePoints = 258;
+
 template <bool DIR>
 __global__ __launch_bounds__(kShadeBlock) void k_proxy_rays(const float *points, const float *normals, int64_t m,
                                                             int S, const float *u, float *o, float *d, float *w,
@@ -176,9 +198,31 @@ __global__ __launch_bounds__(kShadeBlock) void k_proxy_rays(const float *points,
                                                             const Guide g) {
     __shared__ unsigned s_cell[kAimCells];
     __shared__ unsigned long long s_base;
+    __shared__ int s_face[3][kTablePoints];
+    __shared__ double s_P[3][kTablePoints], s_Q[3][kTablePoints], s_factor[3][kTablePoints], s_c0[3][kTablePoints];
     for (int c = threadIdx.x; c < kAimCells; c += kShadeBlock) s_cell[c] = 0;
+    const int64_t block0 = (int64_t)blockIdx.x * kSamplesPerBlock;
+    const int64_t i0 = block0 / S;                               // the block's first point
+    const uint32_t before = (uint32_t)(block0 - i0 * S);         // and its samples in earlier blocks
+    const int64_t in_block = m - block0 < kSamplesPerBlock ? m - block0 : kSamplesPerBlock;
+    const uint32_t n_pts = (before + (uint32_t)in_block - 1u) / (uint32_t)S + 1u;
+    const bool table = g.cdf && n_pts <= (uint32_t)kTablePoints;
+    if (table) {
+        for (uint32_t q = threadIdx.x; q < n_pts; q += kShadeBlock) {
+            const float *x = points + 3 * (i0 + q), *nn = normals + 3 * (i0 + q);
+            const Faces F = guide_faces<DIR>(g, x[0], x[1], x[2], nn[0], nn[1], nn[2]);
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                s_face[ax][q] = F.face[ax];
+                s_P[ax][q] = F.P[ax];
+                s_Q[ax][q] = F.Q[ax];
+                s_factor[ax][q] = F.factor[ax];
+                s_c0[ax][q] = F.c0[ax];
+            }
+        }
+    }
     __syncthreads();
-    const int64_t j0 = (int64_t)blockIdx.x * kSamplesPerBlock + threadIdx.x;
+    const int64_t j0 = block0 + threadIdx.x;
     int cell[kSamplesPerThread];              // aim cell of a live sample, -1 for a dead one
     unsigned rank[kSamplesPerThread];         // its place among the block's samples of that cell
 #pragma unroll
@@ -187,19 +231,32 @@ __global__ __launch_bounds__(kShadeBlock) void k_proxy_rays(const float *points,
         cell[k] = -1;
         rank[k] = 0;
         if (j < m) {
-            const int64_t i = j / S;
+            const uint32_t q = (before + (uint32_t)(k * kShadeBlock) + threadIdx.x) / (uint32_t)S;
+            const int64_t i = i0 + q;
             const float x0 = points[3 * i], x1 = points[3 * i + 1], x2 = points[3 * i + 2];
             const float n0 = normals[3 * i], n1 = normals[3 * i + 1], n2 = normals[3 * i + 2];
             const float u0 = u[3 * j], u1 = u[3 * j + 1], u2 = u[3 * j + 2];
             int f;
             float a, b, inv_density = kInvAreaDensity;
             if (g.cdf) {
-                double factor = 0.0;
-                int bin = 0;
-                int k = guide_cell<DIR>(g, x0, x1, x2, n0, n1, n2, u0, bin, factor);
-                const double pa = k >= 0 ? g.prob[(size_t)bin * g.n_cells + k] * factor / g.area : 0.0;
+                int face = -1;
+                double t, P = 0.0, Q = 0.0, factor = 0.0, c0 = 0.0;
+                if (table) {
+                    const int faces[3] = {s_face[0][q], s_face[1][q], s_face[2][q]};
+                    const double Qs[3] = {s_Q[0][q], s_Q[1][q], s_Q[2][q]};
+                    const int ax = pick_face(faces, Qs, u0, t);
+                    if (ax >= 0) face = s_face[ax][q], P = s_P[ax][q], Q = s_Q[ax][q], factor = s_factor[ax][q], c0 = s_c0[ax][q];
+                } else {
+                    const Faces F = guide_faces<DIR>(g, x0, x1, x2, n0, n1, n2);
+                    const int pick = pick_face(F.face, F.Q, u0, t);
+#pragma unroll
+                    for (int ax = 0; ax < 3; ++ax)
+                        if (pick == ax) face = F.face[ax], P = F.P[ax], Q = F.Q[ax], factor = F.factor[ax], c0 = F.c0[ax];
+                }
+                // a dead sample (no face): any cell, weight 0
+                const int k = face >= 0 ? guide_cell(g, face, P, Q, c0, t) : 0;
+                const double pa = face >= 0 ? g.prob[(size_t)(face >> 3) * g.n_cells + k] * factor / g.area : 0.0;
                 inv_density = pa > 0.0 ? (float)(1.0 / pa) : 0.0f;
-                k = k < 0 ? 0 : k;                    // a dead sample: any cell, weight 0
                 const int gg = g.G * g.G;
                 f = k / gg;
                 const int ca = (k / g.G) % g.G, cb = k % g.G;
@@ -247,14 +304,20 @@ __global__ __launch_bounds__(kShadeBlock) void k_proxy_rays(const float *points,
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {                   // cell counts -> offsets in the block's part of the list
-        unsigned tot = 0;
-        for (int c = 0; c < kAimCells; ++c) {
-            const unsigned n = s_cell[c];
-            s_cell[c] = tot;
-            tot += n;
+    if (threadIdx.x < 64) {                   // cell counts -> offsets in the block's part of the list
+        static_assert(kAimCells % 2 == 0 && kAimCells <= 128, "two cells per lane");
+        const unsigned c = 2 * threadIdx.x;
+        const unsigned a = c < (unsigned)kAimCells ? s_cell[c] : 0u, b = c < (unsigned)kAimCells ? s_cell[c + 1] : 0u;
+        unsigned sum = a + b;
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned v = __shfl_up(sum, off);
+            if ((int)threadIdx.x >= off) sum += v;
         }
-        s_base = tot ? atomicAdd(n_live, (unsigned long long)tot) : 0ull;
+        if (c < (unsigned)kAimCells) {
+            s_cell[c] = sum - a - b;
+            s_cell[c + 1] = sum - b;
+        }
+        if (threadIdx.x == 63) s_base = sum ? atomicAdd(n_live, (unsigned long long)sum) : 0ull;
     }
     __syncthreads();
 #pragma unroll
@@ -346,6 +409,30 @@ constexpr int kCdfChunk = 2048;   // cells staged in LDS at a time
 // count as 0
 __device__ inline double guide_weight(float w) { return w > 0.0f && w < INFINITY ? (double)w : 0.0; }
 
+// run + v[0] + v[1] + ... in that order, the partial sums left in v if `keep`.
+// Sixteen values are read ahead of their additions: the chain is then one
+// FP64 addition per value instead of an LDS access and an addition (1536
+// cells, both sums: 31 us, 39 us one by one).
+__device__ inline double running_sum(double *v, int m, double run, bool keep) {
+    int i = 0;
+    for (; i + 16 <= m; i += 16) {
+        double a[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] = v[i + j];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) a[j] = run = run + a[j];
+        if (keep) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[i + j] = a[j];
+        }
+    }
+    for (; i < m; ++i) {
+        run += v[i];
+        if (keep) v[i] = run;
+    }
+    return run;
+}
+
 __global__ __launch_bounds__(kCdfBlock) void k_guide_cdf(const float *weights, int n, int D, double beta, double *prob,
                                                          double *cdf) {
     __shared__ double s_v[kCdfChunk];
@@ -359,8 +446,7 @@ __global__ __launch_bounds__(kCdfBlock) void k_guide_cdf(const float *weights, i
         const int m = min(kCdfChunk, n - c0);
         for (int i = t; i < m; i += kCdfBlock) s_v[i] = guide_weight(weights[(size_t)(c0 + i) * nb + b]);
         __syncthreads();
-        if (t == 0)
-            for (int i = 0; i < m; ++i) W += s_v[i];
+        if (t == 0) W = running_sum(s_v, m, W, false);
         __syncthreads();
     }
     if (t == 0) {
@@ -379,11 +465,7 @@ __global__ __launch_bounds__(kCdfBlock) void k_guide_cdf(const float *weights, i
             s_v[i] = p;
         }
         __syncthreads();
-        if (t == 0)
-            for (int i = 0; i < m; ++i) {
-                run += s_v[i];
-                s_v[i] = run;
-            }
+        if (t == 0) run = running_sum(s_v, m, run, true);
         __syncthreads();
         for (int i = t; i < m; i += kCdfBlock) cdf[c0 + i + 1] = s_v[i];
         __syncthreads();
