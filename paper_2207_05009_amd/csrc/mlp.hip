@@ -14,8 +14,8 @@
 //   written to LDS, one row per sample, and after a barrier the 84 16x16
 //   blocks of the weight gradients (K = the tile's 64 samples) are split over
 //   the 4 waves, take their operands by transposing LDS reads and accumulate
-//   in registers across the workgroup's tiles; bias gradients are products
-//   with ones.  Each workgroup writes one partial gradient row.
+//   in registers across the workgroup's tiles; bias gradients are sums over
+//   the samples.  Each workgroup writes one partial gradient row.
 //   k_reduce_adam: sums the rows in a fixed order (deterministic), applies
 //   Adam to the float32 master weights and scatters them to the bfloat16
 //   lane-ordered copy the kernels stage.
@@ -145,13 +145,19 @@ __device__ inline void sincos_run5(float x, float *f) {
 // read 4 samples x 16 features, lane i receives feature i of the four) turns
 // the rows into it.  Wave w takes the output positions 16 w .. 16 w + 15 of
 // every layer, so each of its dZ operands serves all input blocks; 21 16x16
-// blocks, and the bias gradients as products with ones, accumulate in
-// registers across the workgroup's tiles.
+// blocks accumulate in registers across the workgroup's tiles; bias
+// gradients are sums over the samples in order, a lane per bias.
 //
-// Bound by LDS throughput (weights, rows and operands through one LDS per
-// CU) with one wave per SIMD.  65536 samples (4 tiles per workgroup): 30 us;
-// 47 us with one row per feature (a 2-byte store per value, 16-byte operand
-// reads off a stride of 36 words, bias gradients as sums over rows).
+// Every sum runs over the samples in the order of the rows before (a row per
+// feature, read in sample order): a gradient added in another order flips
+// bfloat16 roundings of the weights, and after some steps the loss.
+//
+// Bound by the dependency chain of a tile with one wave per SIMD (3.9 us a
+// tile: 40 % of the cycles issue, LDS 30 % busy, matrix cores 16 %).  65536
+// samples (4 tiles per workgroup): 32 us; 47 us with one row per feature (a
+// 2-byte store per value, 16-byte operand reads off a stride of 36 words).
+// Compiled for two waves per SIMD, though LDS admits one, the accumulators stay
+// out of the AGPRs and the 350 moves from and to these per tile go (2 %).
 //
 // Columns of a row.  The features of X stand in slot order, those of H_l and
 // dZ_l in the order the lanes hold them (position_feature), dY takes 16
@@ -335,10 +341,15 @@ __host__ __device__ constexpr int part_param(int q) {
     return m < kOut ? kW5 + m * kHidden + position_feature(16 * w + n) : -1;
 }
 
+// row of a tile's sample: within 32 samples, the first four of every eight,
+// then the others, so that the rows a half wave reads at a time (below) are
+// eight consecutive ones
+__device__ __host__ constexpr int sample_row(int c) { return (c & 32) + ((c >> 3) & 3) * 4 + (c & 3) + ((c >> 2) & 1) * 16; }
+
 // the K = 32 operand over samples 32 grp .. 32 grp + 31 for the 16 columns
-// from c0: lane 16 g + r receives column c0 + r of samples 4 g .. 4 g + 3 and
-// 16 + 4 g .. 16 + 4 g + 3 of the group.  rows: the tile's rows moved to the
-// element this lane reads first (sample 4 g + r / 4, column 4 (r % 4)).
+// from c0: lane 16 g + r receives column c0 + r of samples 8 g .. 8 g + 7 of
+// the group.  rows: the tile's rows moved to the element this lane reads
+// first (row 4 g + r / 4, column 4 (r % 4)).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 __device__ inline bf16x8 sample_operand(uint16_t *rows, int grp, int c0) {
@@ -347,7 +358,20 @@ __device__ inline bf16x8 sample_operand(uint16_t *rows, int grp, int c0) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__global__ __launch_bounds__(256) void k_train_step(const float *o, const float *d, const float *tgt,
+// sum += samples 32 grp .. 32 grp + 31 of a column, in their order; rows: the
+// element of row r / 4, column 4 (r % 4) of the sixteen columns that the 16
+// lanes r of a group take
+__device__ inline void sum_samples(uint16_t *rows, int grp, float &sum) {
+#pragma unroll
+    for (int c = 0; c < 32; c += 4) {
+        const s16x4 v =
+            __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(rows + (32 * grp + sample_row(c)) * kRow));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum += bf2f((uint16_t)v[e]);
+    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_train_step(const float *o, const float *d, const float *tgt,
                                                     int64_t n_pairs, int64_t base, int64_t count,
                                                     int tiles, float inv_batch, const uint16_t *wlane,
                                                     const float *bias, float *part, float *loss_part) {
@@ -382,14 +406,9 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
     f32x4 gacc[21];
 #pragma unroll
     for (int j = 0; j < 21; ++j) gacc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 gb[5];                         // bias gradients: the wave's positions of b1..b4, b5
-#pragma unroll
-    for (int j = 0; j < 5; ++j) gb[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float lsum = 0.0f;
+    float gbias = 0.0f, gb5 = 0.0f, lsum = 0.0f;
     const bf16x8 zero8 = {};
-    const s16x8 one16 = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, one16);
-    uint16_t *row = act + col * kRow;                                // this lane's sample
+    uint16_t *row = act + sample_row(col) * kRow;                    // this lane's sample
     uint16_t *rows = act + (4 * g + (r16 >> 2)) * kRow + 4 * (r16 & 3);   // of sample_operand
 
     // the pair of the lane's sample in tile t (false: past the batch)
@@ -533,13 +552,18 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
         }
         __syncthreads();
 
-        // ---- phase B: weight-gradient blocks over the tile's 64 samples
+        // ---- phase B: weight-gradient blocks over the tile's 64 samples, and the
+        // bias gradients, the samples in order: lane 16 g + r of wave w owns
+        // position 16 w + r of layer g + 1 (every lane sums dY too: cheaper
+        // beside the matrix cores than in one wave alone)
+        float bias_sum = 0.0f, b5_sum = 0.0f;
 #pragma unroll
         for (int grp = 0; grp < 2; ++grp) {
+            sum_samples(rows + 16 * wave - 4 * g * kRow + kColDZ + g * kHidden, grp, bias_sum);
+            sum_samples(rows - 4 * g * kRow + kColDY, grp, b5_sum);
 #pragma unroll
             for (int l = 0; l < 4; ++l) {
                 const bf16x8 dz = sample_operand(rows + 16 * wave, grp, kColDZ + l * kHidden);
-                gb[l] = mfma32(dz, ones, gb[l]);
 #pragma unroll
                 for (int ib = 0; ib < (l == 0 ? 8 : 4); ++ib) {
                     const int slot = l == 0 ? ib : 4 + 4 * l + ib;
@@ -548,9 +572,10 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
                 }
             }
             const bf16x8 dy = sample_operand(rows, grp, kColDY);
-            gb[4] = mfma32(dy, ones, gb[4]);
             gacc[20] = mfma32(dy, sample_operand(rows + 16 * wave, grp, kColH + 3 * kHidden), gacc[20]);
         }
+        gbias += bias_sum;
+        gb5 += b5_sum;
         __syncthreads();
     }
 
@@ -559,12 +584,8 @@ __global__ __launch_bounds__(256) void k_train_step(const float *o, const float 
 #pragma unroll
     for (int slot = 0; slot < 21; ++slot)
         *reinterpret_cast<f32x4 *>(P + ((wave * 21 + slot) * 64 + lane) * 4) = gacc[slot];
-    if (r16 == 0) {                      // all columns of gb are alike
-#pragma unroll
-        for (int l = 0; l < 4; ++l)
-            *reinterpret_cast<f32x4 *>(P + kPartBias + l * kHidden + 16 * wave + 4 * g) = gb[l];
-        if (wave == 0 && g == 0) *reinterpret_cast<f32x4 *>(P + kPartBias + 4 * kHidden) = gb[4];
-    }
+    P[kPartBias + g * kHidden + 16 * wave + r16] = gbias;
+    if (threadIdx.x < 4) P[kPartBias + 4 * kHidden + threadIdx.x] = gb5;
     // loss partial: lanes 0..15 of each wave hold per-sample sums
     float l = lsum;
 #pragma unroll
