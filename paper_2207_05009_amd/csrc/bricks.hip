@@ -8,9 +8,9 @@
 //   k_brick_fill    one block per such brick: its cells' leaves and a
 //                   512-bit occupancy mask;
 //   k_top_extents, k_brick_extents  the empty extents, from the bit rows.
-// Each pass streams its tables once; the extents test cubes of growing size
-// row by row (one 64-bit AND covers a row of the cube), which takes under a
-// millisecond for a depth-9 luminaire of 3M leaves (16k bricks).
+// Each pass streams its tables once; the extents take whole rows of cells as
+// bits (row_codes).  All of it: 0.27 ms for a depth-8 luminaire of 882k leaves,
+// 0.7 ms at depth 9, 3.2 ms at depth 10.
 #include <hip/hip_runtime.h>
 
 #include "lq_internal.h"
@@ -108,45 +108,95 @@ __global__ __launch_bounds__(kBrickCells) void k_brick_fill(const int32_t *child
     if ((t & 63) == 0) occ[(size_t)blockIdx.x * 8 + z] = b;
 }
 
-// Is the cube of m cells from (x, y, z) along octant f empty?  row(z, y)
-// returns the bits of row (z, y) from bit x0 on, x0 the cube's lowest x.
-template <class Row>
-__device__ inline bool cube_empty(int f, int m, int x, int y, int z, Row row) {
-    const int x0 = f & 1 ? x - m + 1 : x, y0 = f & 2 ? y - m + 1 : y, z0 = f & 4 ? z - m + 1 : z;
-    const unsigned long long mask = (1ull << m) - 1ull;
-    for (int k = 0; k < m; ++k)
-        for (int j = 0; j < m; ++j)
-            if (row(z0 + k, y0 + j, x0) & mask) return false;
-    return true;
+// The extents of all cells of a row (z, y), for one octant f, a bit per cell:
+// the rows of the m x m square that the cubes of m cells cover are ORed, the
+// cells along x ORed by shifts; a cell whose bit stays clear has an empty cube.
+// The codes are counted in three bit planes (the cubes are nested).  A wave takes
+// rows of one octant, so its loops are uniform.  All brick tables of a
+// depth-8, 9 and 10 luminaire: 0.27, 0.71 and 3.2 ms; 3.2, 9.7 and 42.7 ms with
+// the cubes tested cell by cell, a lane per cell.
+struct Bits128 {
+    unsigned long long lo, hi;
+};
+__device__ inline unsigned long long bits_or(unsigned long long a, unsigned long long b) { return a | b; }
+__device__ inline unsigned long long bits_andn(unsigned long long a, unsigned long long b) { return a & ~b; }
+__device__ inline unsigned long long bits_and(unsigned long long a, unsigned long long b) { return a & b; }
+__device__ inline unsigned long long bits_xor(unsigned long long a, unsigned long long b) { return a ^ b; }
+__device__ inline bool bits_any(unsigned long long a) { return a != 0; }
+// toward bit 0 (up: away from it); 0 < n < 64
+__device__ inline unsigned long long bits_shift(unsigned long long a, int n, bool up) { return up ? a << n : a >> n; }
+__device__ inline Bits128 bits_or(Bits128 a, Bits128 b) { return {a.lo | b.lo, a.hi | b.hi}; }
+__device__ inline Bits128 bits_andn(Bits128 a, Bits128 b) { return {a.lo & ~b.lo, a.hi & ~b.hi}; }
+__device__ inline Bits128 bits_and(Bits128 a, Bits128 b) { return {a.lo & b.lo, a.hi & b.hi}; }
+__device__ inline Bits128 bits_xor(Bits128 a, Bits128 b) { return {a.lo ^ b.lo, a.hi ^ b.hi}; }
+__device__ inline bool bits_any(Bits128 a) { return (a.lo | a.hi) != 0; }
+__device__ inline Bits128 bits_shift(Bits128 a, int n, bool up) {
+    if (up) return {a.lo << n, (a.hi << n) | (a.lo >> (64 - n))};
+    return {(a.lo >> n) | (a.hi << (64 - n)), a.hi >> n};
 }
 
-template <class Row>
-__device__ inline uint32_t extents(int x, int y, int z, Row row) {
-    uint32_t e = 0;
-    for (int f = 0; f < 8; ++f) {
-        int code = 0;
-        while (code < 7 && cube_empty(f, brick_extent(code + 1), x, y, z, row)) ++code;   // the cubes are nested
-        e |= (uint32_t)code << (3 * f);
+// planes[0..2]: the codes of the cells of `cells` in row (z, y); row(z, y)
+// returns a row's occupied cells.
+template <class B, class Row>
+__device__ inline void row_codes(int f, int z, int y, B cells, Row row, B planes[3]) {
+    const int sy = f & 2 ? -1 : 1, sz = f & 4 ? -1 : 1;
+    B square = {}, open = cells;
+    planes[0] = planes[1] = planes[2] = B{};
+    int done = 0;
+    for (int code = 1; code < 8; ++code) {
+        const int m = brick_extent(code);
+        for (int k = 0; k < m; ++k)
+            for (int j = k < done ? done : 0; j < m; ++j) square = bits_or(square, row(z + sz * k, y + sy * j));
+        done = m;
+        B d = square;
+        int w = 1;
+        for (; 2 * w <= m; w *= 2) d = bits_or(d, bits_shift(d, w, f & 1));
+        if (w < m) d = bits_or(d, bits_shift(d, m - w, f & 1));
+        open = bits_andn(open, d);
+        if (!__any(bits_any(open))) break;
+        B carry = open;
+        for (int b = 0; b < 3; ++b) {
+            const B t = bits_and(planes[b], carry);
+            planes[b] = bits_xor(planes[b], carry);
+            carry = t;
+        }
     }
-    return e;
 }
 
-// a row of up to 128 bits, from bit x0 on (bits outside it are 0)
-__device__ inline unsigned long long row_bits(const unsigned long long *w, int x0) {
-    if (x0 <= -64 || x0 >= 128) return 0ull;
-    if (x0 < 0) return w[0] << -x0;
-    if (x0 >= 64) return w[1] >> (x0 - 64);
-    return x0 == 0 ? w[0] : (w[0] >> x0) | (w[1] << (64 - x0));
-}
+// Block: 64 rows y of slice z (a wave per octant).
+constexpr int kTopRows = 64;
 
-__global__ __launch_bounds__(kMarkBlock) void k_top_extents(const unsigned long long *rows, int bits, uint32_t *top) {
-    const uint32_t i = blockIdx.x * kMarkBlock + threadIdx.x, m = (1u << bits) - 1u;
-    if (i >= (1u << (3 * bits)) || (top[i] & kBrickFull)) return;
-    const int edge = 1 << bits;
-    top[i] = extents(i & m, (i >> bits) & m, i >> (2 * bits), [&](int z, int y, int x0) -> unsigned long long {
-        if (z < 0 || z >= edge || y < 0 || y >= edge) return 0ull;
-        return row_bits(rows + ((size_t)z * edge + y) * 2, x0);
-    });
+__global__ __launch_bounds__(8 * kTopRows) void k_top_extents(const unsigned long long *rows, int bits,
+                                                              uint32_t *top) {
+    __shared__ unsigned long long s_plane[8][3][2][kTopRows];
+    const int edge = 1 << bits, groups = (edge + kTopRows - 1) / kTopRows;
+    const int z = (int)blockIdx.x / groups, y0 = ((int)blockIdx.x % groups) * kTopRows;
+    {
+        const int f = threadIdx.x / kTopRows, r = threadIdx.x % kTopRows;
+        const Bits128 all = {~0ull, ~0ull};
+        Bits128 planes[3];
+        row_codes(f, z, y0 + r, all, [&](int zz, int yy) -> Bits128 {
+            if (zz < 0 || zz >= edge || yy < 0 || yy >= edge) return Bits128{};
+            const unsigned long long *w = rows + ((size_t)zz * edge + yy) * 2;
+            return Bits128{w[0], w[1]};
+        }, planes);
+        for (int b = 0; b < 3; ++b) {
+            s_plane[f][b][0][r] = planes[b].lo;
+            s_plane[f][b][1][r] = planes[b].hi;
+        }
+    }
+    __syncthreads();
+    const int n = (edge - y0 < kTopRows ? edge - y0 : kTopRows) << bits;
+    for (int t = threadIdx.x; t < n; t += 8 * kTopRows) {
+        const int x = t & (edge - 1), r = t >> bits;
+        const size_t i = ((size_t)z * edge + y0) * edge + t;
+        if (top[i] & kBrickFull) continue;
+        uint32_t e = 0;
+        for (int f = 0; f < 8; ++f)
+            for (int b = 0; b < 3; ++b)
+                e |= (uint32_t)((s_plane[f][b][x >> 6][r] >> (x & 63)) & 1u) << (3 * f + b);
+        top[i] = e;
+    }
 }
 
 // The extents of a brick's cells look up to 15 cells beyond it: the rows of
@@ -157,6 +207,7 @@ constexpr int kRows = (2 * kReach + 1) << kBrickBits;  // 40
 __global__ __launch_bounds__(kBrickCells) void k_brick_extents(const uint32_t *top, int bits, const uint32_t *brick_of,
                                                                const unsigned long long *occ, uint32_t *bricks) {
     __shared__ unsigned long long s_row[kRows * kRows];
+    __shared__ uint32_t s_code[8][64];
     const uint32_t i = brick_of[blockIdx.x], m = (1u << bits) - 1u;
     const int edge = 1 << bits, bx = i & m, by = (i >> bits) & m, bz = i >> (2 * bits);
     for (int r = threadIdx.x; r < kRows * kRows; r += kBrickCells) {
@@ -175,9 +226,22 @@ __global__ __launch_bounds__(kBrickCells) void k_brick_extents(const uint32_t *t
     }
     __syncthreads();
     const int t = threadIdx.x, x = t & 7, y = (t >> 3) & 7, z = t >> 6, at = kReach << kBrickBits;
+    {
+        const int f = t >> 6, rz = (t >> 3) & 7, ry = t & 7;     // a wave per octant, a lane per row
+        unsigned long long planes[3];
+        row_codes(f, rz + at, ry + at, 0xFFull << at, [&](int zz, int yy) { return s_row[zz * kRows + yy]; }, planes);
+        s_code[f][t & 63] =
+            (uint32_t)(planes[0] >> at) | (uint32_t)(planes[1] >> at) << 8 | (uint32_t)(planes[2] >> at) << 16;
+    }
+    __syncthreads();
     const size_t j = (size_t)blockIdx.x * kBrickCells + t;
     if (bricks[j] & kBrickFull) return;
-    bricks[j] = extents(x + at, y + at, z + at, [&](int zz, int yy, int x0) { return s_row[zz * kRows + yy] >> x0; });
+    uint32_t e = 0;
+    for (int f = 0; f < 8; ++f) {
+        const uint32_t c = s_code[f][z * 8 + y] >> x;
+        e |= ((c & 1u) | (c >> 7 & 2u) | (c >> 14 & 4u)) << (3 * f);
+    }
+    bricks[j] = e;
 }
 
 __global__ void k_zero_words(unsigned long long *p, size_t n) {
@@ -230,7 +294,9 @@ hipError_t build_bricks(const int32_t *child_skip, int depth, uint32_t **buf, si
                                out, occ);
             hipLaunchKernelGGL(k_brick_extents, dim3(total), dim3(kBrickCells), 0, s, top, bits, brick_of, occ, out);
         }
-        hipLaunchKernelGGL(k_top_extents, dim3(blocks), dim3(kMarkBlock), 0, s, rows, bits, top);
+        const unsigned edge = 1u << bits;
+        hipLaunchKernelGGL(k_top_extents, dim3(edge * ((edge + kTopRows - 1) / kTopRows)), dim3(8 * kTopRows), 0, s, rows,
+                           bits, top);
         e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(s);
     }
