@@ -809,7 +809,7 @@ def main():
                                "frac": round(full_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                                "note": "counts of the validation trace over the full table (densities of "
                                        "leaves below sigma_min and nodes the timed kernel never visits)"},
-                "kernel": "k_query_plain<F32, SH deg 2, sigma_min-pruned table, linear, 8x8 pixel tiles>",
+                "kernel": "k_query_plain<F32, SH deg 2, brick tables of the sigma_min-pruned tree, linear, 8x8 pixel tiles>",
                 "kernel_sources": kernel_sources_hash()}
 
     variants = {}
