@@ -818,15 +818,17 @@ double exponent_change(const FieldArgs &f, int depth) {
     return worst;
 }
 
-// Whether products of four factors E and of four factors L_max - E stay within
-// 2^-100 .. 2^100; E, a mean of the blobs' radiances, lies between them.
+// Whether products of four factors E, of four factors L_max - E and of their
+// quotients stay within 2^-100 .. 2^100; E, a mean of the blobs' radiances,
+// lies between them (quotients between 2^-24 and 2^12).
 bool dc_products_in_range(const FieldArgs &f) {
     float lo = f.l_max, hi = 0.0f;
     for (int k = 0; k < f.nb; ++k) {
         lo = std::min({lo, f.er[k], f.eg[k], f.eb[k]});
         hi = std::max({hi, f.er[k], f.eg[k], f.eb[k]});
     }
-    return lo > 0x1p-24f && f.l_max < 0x1p24f && f.l_max - hi > std::max(0x1p-24f, 0x1p-12f * f.l_max);
+    return lo > 0x1p-24f * std::max(1.0f, f.l_max) && f.l_max < 0x1p24f &&
+           f.l_max - hi > std::max(0x1p-24f, 0x1p-12f * f.l_max);
 }
 
 // The sample loop's blob records (layout at k_distill), as bytes.  Those past

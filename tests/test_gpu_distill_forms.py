@@ -79,3 +79,19 @@ def test_kept_voxels_match_oracle(lq, depth, n_blobs, n_shells, radius):
     o_codes, amb = od.centre_occupancy(od.field_from_params(p), depth)
     assert g_codes.size > 0 and np.all(np.diff(g_codes.astype(np.int64)) > 0)
     assert np.all(np.isin(np.setxor1d(g_codes, o_codes), amb))
+
+
+def test_radiances_far_below_the_ceiling(lq):
+    """Radiances of 1e-6 under a ceiling of 8e6: the DC term's argument is
+    1e-13 per sample, and its product over four samples would leave float32's
+    range.  The bound is that of the forms above."""
+    p = field_params(inputs.TreeSpec(depth=4, n_blobs=5, n_shells=1, sh_degree=0, seed=44, occupancy=0.3))
+    p["radii"] = np.full(5, 0.3)
+    p["l_max"] = 8e6
+    p["emission"] = np.full((5, 3), 1e-6) * np.arange(1, 6)[:, None]
+    print("[gpu] distillation, radiances far below the ceiling", flush=True)
+    codes, sig, sh = lq.distill_leaves(p, 4, 0.01, 9, 5)
+    g_codes = codes.cpu().numpy().view(np.uint32).astype(np.uint64)
+    o_sig, o_sh = od.average_samples(od.field_from_params(p), 4, g_codes, 9, 5)
+    eh = np.abs(sh.cpu().numpy() - o_sh) / np.maximum(np.abs(o_sh), 1e-2)
+    assert g_codes.size > 0 and eh.max() <= RTOL, eh.max()
