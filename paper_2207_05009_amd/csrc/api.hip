@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "launch_shape.h"
 #include "lq_internal.h"
 #include "storage.h"
 
@@ -117,38 +118,42 @@ static __global__ void k_top_grid(const int32_t *table, int32_t *grid) {
     grid[i] = node;
 }
 
-// Leaf rows (DevTree::rows) in the storage type, one thread per 4-byte word:
-// a word's values are read from sigma and sh, the padding is 0.  Streams its
-// input and output once.
+// Leaf rows (DevTree::rows) in the storage type, by 4-byte words (launched with
+// stream_blocks): a word's values are read from sigma and sh, the padding is 0.
+// Streams its input and output once.
 static __global__ void k_rows(const float *sigma, const float *sh, int64_t n, int sh_per_leaf, int row_words,
                               int storage, uint32_t *rows) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n * row_words) return;
-    const int64_t leaf = i / row_words;
-    const int word = (int)(i - leaf * row_words);
-    const auto value = [&](int j) {
-        return j == 0 ? sigma[leaf] : j <= sh_per_leaf ? sh[leaf * sh_per_leaf + (j - 1)] : 0.0f;
-    };
-    const auto half = [&](int j) -> uint32_t {
-        const float v = value(j);
-        return storage == LQ_F16 ? f32_to_f16_rne(v) : f32_to_bf16_rne(v);
-    };
-    rows[i] = storage == LQ_F32 ? __builtin_bit_cast(uint32_t, value(word)) : half(2 * word) | half(2 * word + 1) << 16;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n * row_words; i += step) {
+        const int64_t leaf = i / row_words;
+        const int word = (int)(i - leaf * row_words);
+        const auto value = [&](int j) {
+            return j == 0 ? sigma[leaf] : j <= sh_per_leaf ? sh[leaf * sh_per_leaf + (j - 1)] : 0.0f;
+        };
+        const auto half = [&](int j) -> uint32_t {
+            const float v = value(j);
+            return storage == LQ_F16 ? f32_to_f16_rne(v) : f32_to_bf16_rne(v);
+        };
+        rows[i] = storage == LQ_F32 ? __builtin_bit_cast(uint32_t, value(word))
+                                    : half(2 * word) | half(2 * word + 1) << 16;
+    }
 }
 
-// the rows' densities and coefficients back as float32, one thread per value
+// the rows' densities and coefficients back as float32, by values (launched
+// with stream_blocks)
 static __global__ void k_unpack_rows(const void *rows, int64_t n, int sh_per_leaf, int row_elems, int storage,
                                      float *sigma, float *sh) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int per = sh_per_leaf + 1;
-    if (i >= n * per) return;
-    const int64_t leaf = i / per, at = leaf * row_elems;
-    const int j = (int)(i - leaf * per);
-    const uint32_t bits = storage == LQ_F32 ? static_cast<const uint32_t *>(rows)[at + j]
-                                            : static_cast<const uint16_t *>(rows)[at + j];
-    const float v = stored_to_f32(storage, bits);
-    if (j == 0) sigma[leaf] = v;
-    else sh[leaf * sh_per_leaf + (j - 1)] = v;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n * per; i += step) {
+        const int64_t leaf = i / per, at = leaf * row_elems;
+        const int j = (int)(i - leaf * per);
+        const uint32_t bits = storage == LQ_F32 ? static_cast<const uint32_t *>(rows)[at + j]
+                                                : static_cast<const uint16_t *>(rows)[at + j];
+        const float v = stored_to_f32(storage, bits);
+        if (j == 0) sigma[leaf] = v;
+        else sh[leaf * sh_per_leaf + (j - 1)] = v;
+    }
 }
 
 // Child table without the leaves for which keep_leaf() is false and without
@@ -217,7 +222,7 @@ lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree *
     }
     if (p.n_leaves) {
         const int64_t words = (int64_t)p.n_leaves * (rb / 4);
-        hipLaunchKernelGGL(k_rows, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, p.sigma, p.sh,
+        hipLaunchKernelGGL(k_rows, dim3(stream_blocks(words)), dim3(kStreamThreads), 0, s, p.sigma, p.sh,
                            (int64_t)p.n_leaves, 3 * K, rb / 4, storage, static_cast<uint32_t *>(t->d_rows));
     }
     DevTree &dt = t->t;
@@ -398,7 +403,7 @@ lq_status lq_octree_download(const lq_octree *t, int32_t *child, float *sigma, f
         (void)hipGetLastError();
         return fail(LQ_ERR_OOM, "device scratch of the download");
     }
-    hipLaunchKernelGGL(k_unpack_rows, dim3((unsigned)((n * (1 + sh_per_leaf) + 255) / 256)), dim3(256), 0, nullptr,
+    hipLaunchKernelGGL(k_unpack_rows, dim3(stream_blocks(n * (1 + sh_per_leaf))), dim3(kStreamThreads), 0, nullptr,
                        dt.rows, (int64_t)n, sh_per_leaf, dt.row_elems, dt.storage, vals, vals + n);
     e = hipGetLastError();
     if (e == hipSuccess && sigma) e = hipMemcpy(sigma, vals, n * 4, hipMemcpyDeviceToHost);

@@ -1,0 +1,20 @@
+// launch_shape.h -- how launches are sized (host arithmetic, plain C++).
+#pragma once
+
+#include <stdint.h>
+
+namespace lq {
+
+// Blocks of kStreamThreads for a kernel that strides over n items.  HIP takes
+// fewer than 2^32 threads in a dimension, and the largest trees hold more words
+// (a float32 leaf of SH degree 4 has 128, so 2^25 leaves are beyond it): at most
+// kStreamBlocks, each thread then taking several items.  All tables up to 2^30
+// words keep a thread per word.
+constexpr unsigned kStreamThreads = 256;
+constexpr unsigned kStreamBlocks = 1u << 22;
+inline unsigned stream_blocks(uint64_t n) {
+    const uint64_t blocks = n / kStreamThreads + (n % kStreamThreads != 0);
+    return (unsigned)(blocks < 1 ? 1 : blocks > kStreamBlocks ? kStreamBlocks : blocks);
+}
+
+}  // namespace lq

@@ -1,0 +1,43 @@
+"""Launch sizes (launch_shape.h, host arithmetic) built with g++."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2207_05009_amd", "csrc")
+
+
+def _run(tmp_path, program):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("needs g++")
+    src, exe = tmp_path / "shape.cpp", tmp_path / "shape"
+    src.write_text(program)
+    subprocess.run([gxx, "-std=c++17", "-O2", "-Wall", "-Werror", f"-I{CSRC}", "-o", str(exe), str(src)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout == "ok\n", out.stdout
+
+
+def test_streaming_launches_fit_a_grid_and_cover_every_word(tmp_path):
+    """Every admitted tree (up to 2^30 leaves of 16 to 128 words): fewer than
+    2^32 threads, all words reached, and a thread per word where that fits."""
+    _run(tmp_path, r"""
+#include "launch_shape.h"
+#include <cstdio>
+int main() {
+    using namespace lq;
+    const uint64_t leaves[] = {0, 1, 15, 16, 17, 882000, 33554431, 33554432, 56512728, 134217728, 1ull << 30};
+    const uint64_t per_leaf[] = {1, 4, 13, 16, 28, 32, 64, 76, 128};
+    for (uint64_t n : leaves)
+        for (uint64_t words : per_leaf) {
+            const uint64_t items = n * words, blocks = stream_blocks(items), threads = blocks * kStreamThreads;
+            if (blocks < 1 || threads >= 1ull << 32) { std::printf("%llu items: %llu blocks\n", (unsigned long long)items, (unsigned long long)blocks); return 1; }
+            if (items <= 1ull << 30 && threads < items) { std::printf("%llu items: not a thread each\n", (unsigned long long)items); return 1; }
+            if (threads >= items + kStreamThreads && blocks > 1) { std::printf("%llu items: idle blocks\n", (unsigned long long)items); return 1; }
+        }
+    std::printf("ok\n");
+    return 0;
+}
+""")
