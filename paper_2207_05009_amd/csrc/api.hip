@@ -139,21 +139,51 @@ static __global__ void k_rows(const float *sigma, const float *sh, int64_t n, in
     }
 }
 
-// the rows' densities and coefficients back as float32, by values (launched
-// with stream_blocks)
-static __global__ void k_unpack_rows(const void *rows, int64_t n, int sh_per_leaf, int row_elems, int storage,
-                                     float *sigma, float *sh) {
-    const int per = sh_per_leaf + 1;
+// values first .. first + per - 1 of every row back as float32, contiguous per
+// leaf (launched with stream_blocks)
+static __global__ void k_unpack_rows(const void *rows, int64_t n, int first, int per, int row_elems, int storage,
+                                     float *out) {
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n * per; i += step) {
-        const int64_t leaf = i / per, at = leaf * row_elems;
-        const int j = (int)(i - leaf * per);
-        const uint32_t bits = storage == LQ_F32 ? static_cast<const uint32_t *>(rows)[at + j]
-                                                : static_cast<const uint16_t *>(rows)[at + j];
-        const float v = stored_to_f32(storage, bits);
-        if (j == 0) sigma[leaf] = v;
-        else sh[leaf * sh_per_leaf + (j - 1)] = v;
+        const int64_t leaf = i / per, at = leaf * row_elems + first + (i - leaf * per);
+        const uint32_t bits = storage == LQ_F32 ? static_cast<const uint32_t *>(rows)[at]
+                                                : static_cast<const uint16_t *>(rows)[at];
+        out[i] = stored_to_f32(storage, bits);
     }
+}
+
+// Device scratch for a slice of leaves (slice_leaves), smaller where the card
+// has no room for that; p stays null when there is none for a single leaf.
+struct SliceScratch {
+    float *p = nullptr;
+    size_t leaves;
+    SliceScratch(size_t n, size_t bytes) : leaves(slice_leaves(n, bytes)) {
+        while (hipMalloc((void **)&p, leaves * bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+            if (leaves == 1) return;
+            leaves = (leaves + 1) / 2;
+        }
+    }
+    ~SliceScratch() { (void)hipFree(p); }
+    SliceScratch(const SliceScratch &) = delete;
+};
+
+// values first .. first + per - 1 of every leaf of t to host memory
+static lq_status download_values(const DevTree &t, int first, int per, float *host) {
+    const size_t n = (size_t)t.n_leaves, row_bytes = (size_t)t.row_elems * (t.storage == LQ_F32 ? 4 : 2);
+    const SliceScratch slice(n, (size_t)per * 4);
+    if (!slice.p) return fail(LQ_ERR_OOM, "device scratch of the download");
+    for (size_t at = 0; at < n; at += slice.leaves) {
+        const size_t m = n - at < slice.leaves ? n - at : slice.leaves;
+        hipLaunchKernelGGL(k_unpack_rows, dim3(stream_blocks(m * per)), dim3(kStreamThreads), 0, nullptr,
+                           static_cast<const char *>(t.rows) + at * row_bytes, (int64_t)m, first, per, t.row_elems,
+                           t.storage, slice.p);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpy(host + at * per, slice.p, m * per * 4, hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return hip_fail(e, "reading the leaf rows");
+    }
+    return LQ_OK;
 }
 
 // Child table without the leaves for which keep_leaf() is false and without
@@ -395,21 +425,10 @@ lq_status lq_octree_download(const lq_octree *t, int32_t *child, float *sigma, f
     const DevTree &dt = t->t;
     if (child && (e = hipMemcpy(child, t->d_child, (size_t)dt.n_nodes * 32, hipMemcpyDeviceToHost)) != hipSuccess)
         return hip_fail(e, "reading the child table");
-    if ((!sigma && !sh) || dt.n_leaves == 0) return LQ_OK;
-    const size_t n = (size_t)dt.n_leaves;
-    const int sh_per_leaf = 3 * dt.K;
-    float *vals = nullptr;   // densities, then coefficients
-    if (hipMalloc((void **)&vals, n * (1 + sh_per_leaf) * 4) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(LQ_ERR_OOM, "device scratch of the download");
-    }
-    hipLaunchKernelGGL(k_unpack_rows, dim3(stream_blocks(n * (1 + sh_per_leaf))), dim3(kStreamThreads), 0, nullptr,
-                       dt.rows, (int64_t)n, sh_per_leaf, dt.row_elems, dt.storage, vals, vals + n);
-    e = hipGetLastError();
-    if (e == hipSuccess && sigma) e = hipMemcpy(sigma, vals, n * 4, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && sh) e = hipMemcpy(sh, vals + n, n * sh_per_leaf * 4, hipMemcpyDeviceToHost);
-    (void)hipFree(vals);
-    return e == hipSuccess ? LQ_OK : hip_fail(e, "reading the leaf rows");
+    if (dt.n_leaves == 0) return LQ_OK;
+    lq_status st = sigma ? download_values(dt, 0, 1, sigma) : LQ_OK;
+    if (st == LQ_OK && sh) st = download_values(dt, 1, 3 * dt.K, sh);
+    return st;
 }
 
 lq_status lq_octree_info(const lq_octree *t, int64_t *device_bytes, int32_t *n_nodes, int32_t *n_leaves,

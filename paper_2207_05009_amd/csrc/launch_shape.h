@@ -17,4 +17,14 @@ inline unsigned stream_blocks(uint64_t n) {
     return (unsigned)(blocks < 1 ? 1 : blocks > kStreamBlocks ? kStreamBlocks : blocks);
 }
 
+// Leaves per slice for work that goes through a tree's leaves with scratch of
+// `bytes` per leaf, so that a large tree does not need as much again: 64 MiB, a
+// few milliseconds of copying to the host, beside which a launch per slice does
+// not count.
+constexpr uint64_t kSliceBytes = (uint64_t)64 << 20;
+inline uint64_t slice_leaves(uint64_t leaves, uint64_t bytes) {
+    const uint64_t fit = kSliceBytes / bytes;
+    return leaves < 1 ? 1 : fit < leaves ? fit : leaves;
+}
+
 }  // namespace lq

@@ -41,3 +41,24 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_slices_stay_within_their_bytes_and_cover_every_leaf(tmp_path):
+    _run(tmp_path, r"""
+#include "launch_shape.h"
+#include <cstdio>
+int main() {
+    using namespace lq;
+    const uint64_t leaves[] = {0, 1, 2, 100, 55188, 882000, 16777216, 16777217, 1ull << 30}, bytes[] = {4, 12, 108, 300, 304};
+    for (uint64_t n : leaves)
+        for (uint64_t b : bytes) {
+            const uint64_t m = slice_leaves(n, b);
+            if (m < 1 || m * b > kSliceBytes || (n && m > n) || (n * b <= kSliceBytes && n && m != n)) {
+                std::printf("%llu leaves of %llu: %llu\n", (unsigned long long)n, (unsigned long long)b, (unsigned long long)m);
+                return 1;
+            }
+        }
+    std::printf("ok\n");
+    return 0;
+}
+""")
