@@ -220,6 +220,32 @@ static std::vector<int32_t> prune_tree(const lq_octree_desc *d, const std::vecto
     return out;
 }
 
+// The rows of p's leaves, those in host memory by way of slices on the device.
+static lq_status pack_rows(const OctreeParts &p, int sh_per_leaf, int rb, int storage, void *rows) {
+    const size_t n = (size_t)p.n_leaves;
+    const auto pack = [&](const float *sigma, const float *sh, size_t at, size_t m) {
+        hipLaunchKernelGGL(k_rows, dim3(stream_blocks(m * (rb / 4))), dim3(kStreamThreads), 0, nullptr, sigma, sh,
+                           (int64_t)m, sh_per_leaf, rb / 4, storage,
+                           reinterpret_cast<uint32_t *>(static_cast<char *>(rows) + at * rb));
+        return hipGetLastError();
+    };
+    hipError_t e = hipSuccess;
+    if (!p.leaves_on_host) {
+        e = pack(p.sigma, p.sh, 0, n);
+        return e == hipSuccess ? LQ_OK : hip_fail(e, "packing the leaf rows");
+    }
+    const SliceScratch slice(n, (size_t)(1 + sh_per_leaf) * 4);
+    if (!slice.p) return fail(LQ_ERR_OOM, "device scratch of the leaf rows");
+    for (size_t at = 0; at < n && e == hipSuccess; at += slice.leaves) {
+        const size_t m = n - at < slice.leaves ? n - at : slice.leaves;
+        float *sh = slice.p + m;
+        e = hipMemcpy(slice.p, p.sigma + at, m * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(sh, p.sh + at * sh_per_leaf, m * sh_per_leaf * 4, hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = pack(slice.p, sh, at, m);
+    }
+    return e == hipSuccess ? LQ_OK : hip_fail(e, "uploading the leaves");
+}
+
 lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree **out) {
     lq_octree *t = new (std::nothrow) lq_octree();
     if (!t) {
@@ -250,10 +276,10 @@ lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree *
         hipLaunchKernelGGL(k_top_grid, dim3(kTopCells / 256), dim3(256), 0, s, p.child, t->d_top);
         hipLaunchKernelGGL(k_top_grid, dim3(kTopCells / 256), dim3(256), 0, s, p.child_skip, t->d_top + kTopCells);
     }
-    if (p.n_leaves) {
-        const int64_t words = (int64_t)p.n_leaves * (rb / 4);
-        hipLaunchKernelGGL(k_rows, dim3(stream_blocks(words)), dim3(kStreamThreads), 0, s, p.sigma, p.sh,
-                           (int64_t)p.n_leaves, 3 * K, rb / 4, storage, static_cast<uint32_t *>(t->d_rows));
+    const lq_status st = p.n_leaves ? pack_rows(p, 3 * K, rb, storage, t->d_rows) : LQ_OK;
+    if (st != LQ_OK) {
+        lq_free_octree(t);
+        return st;
     }
     DevTree &dt = t->t;
     dt.child = t->d_child;
@@ -312,7 +338,6 @@ lq_status lq_load_octree_desc(const lq_octree_desc *desc, int storage, int devic
     if (device < 0 || device >= ndev) return fail(LQ_ERR_INVALID_ARG, "device index out of range");
     if ((e = hipSetDevice(device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
 
-    const int64_t nl = desc->n_leaves, sh_per_leaf = 3 * (desc->sh_degree + 1) * (desc->sh_degree + 1);
     const std::vector<int32_t> skip = prune_tree(desc, bfs, [&](int64_t leaf) {
         // density as stored (after rounding), compared like the kernel does
         return as_stored(storage, desc->sigma[leaf]) >= desc->sigma_min;
@@ -327,33 +352,23 @@ lq_status lq_load_octree_desc(const lq_octree_desc *desc, int storage, int devic
     p.sigma_min = desc->sigma_min;
     p.alpha_max = desc->alpha_max;
     const size_t child_bytes = (size_t)desc->n_nodes * 32, skip_bytes = skip.size() * 4;
-    float *leaves = nullptr;   // densities, then coefficients
-    auto release = [&]() {
-        (void)hipFree(p.child);
-        (void)hipFree(p.child_skip);
-        (void)hipFree(leaves);
-    };
     if (hipMalloc((void **)&p.child, child_bytes) != hipSuccess ||
-        hipMalloc((void **)&p.child_skip, skip_bytes) != hipSuccess ||
-        (nl && hipMalloc((void **)&leaves, (size_t)nl * (1 + sh_per_leaf) * 4) != hipSuccess)) {
+        hipMalloc((void **)&p.child_skip, skip_bytes) != hipSuccess) {
         (void)hipGetLastError();
-        release();
+        (void)hipFree(p.child);
         return fail(LQ_ERR_OOM, "device allocation of the tree tables failed");
     }
     e = hipMemcpy(p.child, desc->child, child_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p.child_skip, skip.data(), skip_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess && nl) e = hipMemcpy(leaves, desc->sigma, (size_t)nl * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess && nl)
-        e = hipMemcpy(leaves + nl, desc->sh, (size_t)nl * sh_per_leaf * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
-        release();
+        (void)hipFree(p.child);
+        (void)hipFree(p.child_skip);
         return hip_fail(e, "uploading the tree");
     }
-    p.sigma = leaves;
-    p.sh = leaves + nl;
-    st = make_octree(p, storage, device, out);
-    (void)hipFree(leaves);
-    return st;
+    p.sigma = desc->sigma;
+    p.sh = desc->sh;
+    p.leaves_on_host = true;
+    return make_octree(p, storage, device, out);
 }
 
 lq_status lq_load_octree(const char *path, int storage, int device, lq_octree **out) {

@@ -130,14 +130,16 @@ hipError_t launch_query_multi(int storage, int sh_degree, const DevTree *trees, 
 hipError_t build_bricks(const int32_t *child_skip, int depth, uint32_t **buf, size_t *bytes, const uint32_t **brick_top,
                         const uint32_t **bricks);
 
-// An octree on `device` (current) from device tables: its child tables (which
-// it takes over) and its leaves' densities and coefficients (read during the
-// call).  On failure the child tables are freed.  Synchronous.
+// An octree on `device` (current) from its child tables in device memory (which
+// it takes over) and its leaves' densities and coefficients in host or device
+// memory (read during the call).  On failure the child tables are freed.
+// Synchronous.
 struct OctreeParts {
     int32_t max_depth, sh_degree, n_nodes, n_skip_nodes, n_leaves;
     float l_max, sigma_min, alpha_max;
     int32_t *child, *child_skip;
     const float *sigma, *sh;
+    bool leaves_on_host;
 };
 lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree **out);
 // the scalars of a tree: LQ_OK, or the error a loader returns for them

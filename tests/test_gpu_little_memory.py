@@ -3,6 +3,8 @@ needs device memory in proportion to the float32 values of all leaves."""
 import numpy as np
 import pytest
 
+import inputs
+
 pytestmark = pytest.mark.gpu
 
 MB = 1 << 20
@@ -44,4 +46,16 @@ def test_download_needs_no_room_for_the_whole_result():
     with Filled(200 * MB):
         out = tree.download()
     assert np.array_equal(out["sigma"], before[0]) and np.array_equal(out["sh"], before[1])
+    tree.free()
+
+
+def test_load_needs_no_room_for_a_copy_of_the_leaves():
+    import torch
+    from paper_2207_05009_amd import lumiq
+    t = inputs.random_tree(7, 0.5, seed=3, sh_degree=4)               # 1.05M leaves: 512 MB of rows, 304 MB of values
+    tables = 64 * len(t.child) + 2048 * 4096                          # both child tables, bricks
+    with Filled(512 * t.n_leaves + tables + 150 * MB):
+        tree = lumiq.Octree(t, "f32")
+        out = tree.download()
+    assert np.array_equal(out["sigma"], t.sigma) and np.array_equal(out["sh"].reshape(t.sh.shape), t.sh)
     tree.free()
