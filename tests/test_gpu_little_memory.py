@@ -59,3 +59,19 @@ def test_load_needs_no_room_for_a_copy_of_the_leaves():
         out = tree.download()
     assert np.array_equal(out["sigma"], t.sigma) and np.array_equal(out["sh"].reshape(t.sh.shape), t.sh)
     tree.free()
+
+
+def test_build_gives_its_scratch_back_before_the_rows():
+    import torch
+    from paper_2207_05009_amd import lumiq
+    n, g = 3 << 20, torch.Generator(device="cuda").manual_seed(6)
+    codes = torch.arange(n, dtype=torch.int32, device="cuda") * 5
+    sigma, sh = torch.rand(n, generator=g, device="cuda"), torch.randn((n, 3, 9), generator=g, device="cuda")
+    tree = lumiq.octree_from_leaves(8, 2, codes, sigma, sh)           # 403 MB of rows; 120 MB of scratch before them
+    need, ref = tree.info()["device_bytes"], tree.download()
+    tree.free()
+    with Filled(need + 50 * MB):
+        tree = lumiq.octree_from_leaves(8, 2, codes, sigma, sh)
+    out = tree.download()
+    assert all(np.array_equal(out[k], ref[k]) for k in ref)
+    tree.free()
