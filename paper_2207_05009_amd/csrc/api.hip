@@ -19,7 +19,7 @@ struct lq_octree {
     int32_t *d_child;
     int32_t *d_child_skip;
     int32_t *d_top;   // grids of child and child_skip, or null (depth <= kTopLevel)
-    uint32_t *d_bricks;   // brick tables of child_skip
+    uint32_t *d_bricks;   // brick tables of child_skip, or null
     void *d_rows;
     int64_t bytes;
 };
@@ -301,11 +301,14 @@ lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree *
     hipError_t e = hipGetLastError();
     if (e == hipSuccess)
         e = build_bricks(t->d_child_skip, p.max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
-    if (e != hipSuccess) {
+    if (e == hipErrorOutOfMemory) {   // no room for bricks: the queries march child_skip
         (void)hipGetLastError();
+        brick_bytes = 0;
+        e = hipSuccess;
+    }
+    if (e != hipSuccess) {
         lq_free_octree(t);
-        return e == hipErrorOutOfMemory ? fail(LQ_ERR_OOM, "device allocation of the brick tables failed")
-                                        : hip_fail(e, "building the tree's tables");
+        return hip_fail(e, "building the tree's tables");
     }
     t->bytes = (int64_t)((size_t)p.n_nodes * 32 + (size_t)p.n_skip_nodes * 32 + top_bytes + brick_bytes + row_total);
     *out = t;
@@ -683,7 +686,11 @@ lq_status lq_query_radiance_multi(const lq_octree *const *trees, int32_t n_trees
     if (alpha && (st = check_dev(alpha, n * 4, dev, "alpha")) != LQ_OK) return st;
     hipStream_t s = (hipStream_t)hip_stream;
     std::vector<DevTree> host_trees(n_trees);
-    for (int k = 0; k < n_trees; ++k) host_trees[k] = trees[k]->t;
+    bool bricks = true;
+    for (int k = 0; k < n_trees; ++k) {
+        host_trees[k] = trees[k]->t;
+        bricks = bricks && host_trees[k].bricks;
+    }
     const size_t tb = sizeof(DevTree) * (size_t)n_trees, ob = sizeof(int64_t) * (size_t)(n_trees + 1);
     unsigned char *buf = nullptr;
     if ((e = hipMallocAsync((void **)&buf, tb + ob, s)) != hipSuccess) return hip_fail(e, "hipMallocAsync");
@@ -693,7 +700,7 @@ lq_status lq_query_radiance_multi(const lq_octree *const *trees, int32_t n_trees
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess)
         e = launch_query_multi(trees[0]->t.storage, trees[0]->t.sh_degree, reinterpret_cast<DevTree *>(buf),
-                               reinterpret_cast<int64_t *>(buf + tb), n_trees, a, s);
+                               reinterpret_cast<int64_t *>(buf + tb), n_trees, bricks, a, s);
     (void)hipFreeAsync(buf, s);
     if (e != hipSuccess) return hip_fail(e, "launching the multi-tree query");
     return LQ_OK;

@@ -43,6 +43,9 @@ constexpr int kTopCells = 1 << (3 * kTopLevel);
 // octant's directions holds no leaf; cells outside the grid count as empty.
 // One entry thus says, for the cell a ray is in, either which leaf it is or
 // how far the ray may go at once, in place of a descent from node to node.
+// The tables take 2 KB per brick that holds a leaf, up to 4 GB at depth 10.  A
+// tree that loads onto a card without room for them goes without: its plain
+// queries march child_skip, to the same results.
 constexpr int kBrickBits = 3;
 constexpr int kBrickCells = 1 << (3 * kBrickBits);
 constexpr uint32_t kBrickFull = 0x80000000u;
@@ -55,7 +58,7 @@ struct DevTree {
     const int32_t *child_skip;
     const int32_t *top;        // [kTopCells] grid of `child`, or null
     const int32_t *top_skip;   // [kTopCells] grid of `child_skip`, or null
-    const uint32_t *brick_top;
+    const uint32_t *brick_top;   // null, like bricks, for a tree without brick tables
     const uint32_t *bricks;
     const void *rows;
     int32_t depth, sh_degree, K, storage;
@@ -121,9 +124,9 @@ __host__ __device__ inline uint32_t tile_order_pixel(uint32_t v, uint32_t w, uin
 // launch the emission query; returns hipSuccess or the launch error
 hipError_t launch_query(const DevTree &t, const QueryArgs &a, bool trace, hipStream_t s);
 // several trees of one storage type and SH degree (2 or 3) in one launch;
-// trees/offsets are device arrays
+// trees/offsets are device arrays; bricks: every tree has brick tables
 hipError_t launch_query_multi(int storage, int sh_degree, const DevTree *trees, const int64_t *offsets,
-                              int n_trees, const QueryArgs &a, hipStream_t s);
+                              int n_trees, bool bricks, const QueryArgs &a, hipStream_t s);
 
 // Brick tables of the pruned child table (device memory) of a tree: one new
 // allocation *buf of *bytes that holds both tables.  Synchronous.

@@ -97,7 +97,7 @@ __device__ inline int64_t range_begin(int x, int64_t n) { return n * x / kRanges
 enum { kOrderAny = 0, kOrderBatch = 1, kOrderTiles = 2 };
 
 // How a lane walks its ray.  OctreeWalk: node by node through the octree
-// (the validation variants).  The block copies the tree's top grid into LDS,
+// (the validation variants, and trees without brick tables).  The block copies the tree's top grid into LDS,
 // and each lane keeps its node path there.
 template <int ST, int DEG, bool ACC64, bool TRACE_, bool SKIP, int MODEL>
 struct OctreeWalk {
@@ -231,8 +231,9 @@ __device__ inline void persistent_query(const QueryArgs &a, unsigned long long *
     }
 }
 
-// The validation kernels: traces, FP64 accumulation, every leaf composited;
-// the transmittance model and the ray order come from the arguments.
+// The validation kernels (traces, FP64 accumulation, every leaf composited) and
+// the plain query of a tree without brick tables; the transmittance model and
+// the ray order come from the arguments.
 template <int ST, int DEG, bool ACC64, bool TRACE, bool SKIP>
 __global__ __launch_bounds__(kBlock) void k_query(const DevTree t, const QueryArgs a,
                                                   unsigned long long *queue) {
@@ -385,6 +386,7 @@ hipError_t launch_deg(const DevTree &t, const QueryArgs &a, bool trace, hipStrea
     if (full) return acc64 ? launch_checked<ST, DEG, true, false, false>(t, a, s)
                            : launch_persistent<false>(k_query_full<ST, DEG>, a, a.counters, s, t, a);
     if (acc64) return launch_checked<ST, DEG, true, false, true>(t, a, s);
+    if (!t.bricks) return launch_checked<ST, DEG, false, false, true>(t, a, s);
     return a.model == LQ_EXP ? launch_plain<ST, DEG, LQ_EXP>(t, a, s) : launch_plain<ST, DEG, LQ_LINEAR>(t, a, s);
 }
 
@@ -401,8 +403,8 @@ hipError_t launch_st(const DevTree &t, const QueryArgs &a, bool trace, hipStream
 }
 
 template <int ST, int DEG>
-hipError_t launch_multi_deg(const DevTree *trees, const int64_t *offsets, int n_trees, const QueryArgs &a,
-                            hipStream_t s) {
+hipError_t launch_multi_deg(const DevTree *trees, const int64_t *offsets, int n_trees, bool bricks,
+                            const QueryArgs &a, hipStream_t s) {
     const bool acc64 = (a.flags & LQ_FP64_ACCUM) != 0;
     const bool full = (a.flags & LQ_NO_SIGMA_SKIP) != 0;
     const auto checked = [&](auto kern) {
@@ -413,15 +415,16 @@ hipError_t launch_multi_deg(const DevTree *trees, const int64_t *offsets, int n_
     };
     if (full) return acc64 ? checked(k_query_multi<ST, DEG, true, false>) : checked(k_query_multi<ST, DEG, false, false>);
     if (acc64) return checked(k_query_multi<ST, DEG, true, true>);
+    if (!bricks) return checked(k_query_multi<ST, DEG, false, true>);
     return a.model == LQ_EXP ? plain(k_query_multi_plain<ST, DEG, LQ_EXP>) : plain(k_query_multi_plain<ST, DEG, LQ_LINEAR>);
 }
 
 template <int ST>
-hipError_t launch_multi_st(int deg, const DevTree *trees, const int64_t *offsets, int n_trees, const QueryArgs &a,
-                           hipStream_t s) {
+hipError_t launch_multi_st(int deg, const DevTree *trees, const int64_t *offsets, int n_trees, bool bricks,
+                           const QueryArgs &a, hipStream_t s) {
     switch (deg) {
-        case 2: return launch_multi_deg<ST, 2>(trees, offsets, n_trees, a, s);
-        case 3: return launch_multi_deg<ST, 3>(trees, offsets, n_trees, a, s);
+        case 2: return launch_multi_deg<ST, 2>(trees, offsets, n_trees, bricks, a, s);
+        case 3: return launch_multi_deg<ST, 3>(trees, offsets, n_trees, bricks, a, s);
     }
     return hipErrorInvalidValue;
 }

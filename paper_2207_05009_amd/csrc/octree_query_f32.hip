@@ -8,8 +8,8 @@ hipError_t launch_query_f32(const DevTree &t, const QueryArgs &a, bool trace, hi
 }
 
 hipError_t launch_query_multi_f32(int sh_degree, const DevTree *trees, const int64_t *offsets, int n_trees,
-                                   const QueryArgs &a, hipStream_t s) {
-    return launch_multi_st<LQ_F32>(sh_degree, trees, offsets, n_trees, a, s);
+                                   bool bricks, const QueryArgs &a, hipStream_t s) {
+    return launch_multi_st<LQ_F32>(sh_degree, trees, offsets, n_trees, bricks, a, s);
 }
 
 }  // namespace lq

@@ -1,5 +1,6 @@
-"""Loading and reading back a tree on a card that holds little beside it: neither
-needs device memory in proportion to the float32 values of all leaves."""
+"""Loading, building and reading back a tree on a card that holds little beside
+it: none needs device memory in proportion to the float32 values of all leaves,
+and a tree without room for its brick tables answers without them."""
 import numpy as np
 import pytest
 
@@ -75,3 +76,38 @@ def test_build_gives_its_scratch_back_before_the_rows():
     out = tree.download()
     assert all(np.array_equal(out[k], ref[k]) for k in ref)
     tree.free()
+
+
+def test_tree_without_room_for_bricks_answers_the_same():
+    """600,000 leaves scattered over depth 10, nearly each in a brick of its own:
+    1.2 GB of bricks beside 0.2 GB of other tables.  The octree march visits the
+    same leaves over the same segments; only a segment that starts at an edge or a
+    corner may round differently, within a few float32 ulp of each of its terms."""
+    import torch
+    from paper_2207_05009_amd import lumiq
+    g = torch.Generator(device="cuda").manual_seed(8)
+    codes = torch.unique(torch.randint(0, 1 << 30, (600000,), generator=g, device="cuda")).to(torch.int32)
+    n = codes.numel()
+    sigma = torch.rand(n, generator=g, device="cuda") * 60.0
+    sh = torch.randn((n, 3, 9), generator=g, device="cuda")
+    bricks = 2048 * torch.unique(codes >> 9).numel()
+    trees = [lumiq.octree_from_leaves(10, 2, codes, sigma, sh, storage="f16")]
+    need = trees[0].info()["device_bytes"] - bricks
+    with Filled(need + 300 * MB):
+        trees.append(lumiq.octree_from_leaves(10, 2, codes, sigma, sh, storage="f16"))
+        assert trees[1].info()["device_bytes"] <= need
+    o, d = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in inputs.rays.room_to_proxy(1 << 18, 9))
+    u = torch.rand((4096, 8, 3), generator=g, device="cuda")
+    up = torch.tensor([0.0, 0.0, 1.0], device="cuda").expand(4096, 3).contiguous()
+    p = torch.rand((4096, 3), generator=g, device="cuda") * 4.0 - 2.0
+    p[:, 2] = -1.5
+    for model in ("linear", "exp"):
+        res = [[*t.query(o, d, model=model), *t.query_image(o, d, 512, 512, model=model),
+                *lumiq.query_multi([t, t, trees[0]], [0, 1000, 1000, 1 << 18], o, d, model=model),
+                t.proxy_irradiance(p, up, u, model=model)[0]] for t in trees]
+        torch.cuda.synchronize()
+        for a, b in zip(*res):
+            assert float(a.sum()) > 0
+            assert float((a == b).float().mean()) > 0.999 and torch.allclose(a, b, rtol=1e-5, atol=1e-6)
+    for t in trees:
+        t.free()
