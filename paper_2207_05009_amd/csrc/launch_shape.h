@@ -3,6 +3,10 @@
 
 #include <stdint.h>
 
+#include <map>
+#include <mutex>
+#include <utility>
+
 namespace lq {
 
 // Blocks of kStreamThreads for a kernel that strides over n items.  HIP takes
@@ -26,5 +30,23 @@ inline uint64_t slice_leaves(uint64_t leaves, uint64_t bytes) {
     const uint64_t fit = kSliceBytes / bytes;
     return leaves < 1 ? 1 : fit < leaves ? fit : leaves;
 }
+
+// Blocks of a kernel that a device holds at once.  ask() finds them, once per
+// device and kernel: kernels of one signature have register budgets of their own
+// (a 3-wave kernel's blocks would leave a 5-wave one's launch under-filled).
+class ResidentBlocks {
+public:
+    template <class Ask>
+    int get(int device, const void *kernel, Ask ask) {
+        std::lock_guard<std::mutex> lock(mu_);
+        const auto key = std::make_pair(device, kernel);
+        const auto it = known_.find(key);
+        return it != known_.end() ? it->second : known_[key] = ask();
+    }
+
+private:
+    std::mutex mu_;
+    std::map<std::pair<int, const void *>, int> known_;
+};
 
 }  // namespace lq

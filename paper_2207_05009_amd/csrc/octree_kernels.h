@@ -34,13 +34,11 @@
 // the rest of one tile with rays of the next (refill below 16 busy lanes)
 // costs more in cache lines than the idle lanes do: 0.93 -> 0.77 ms, and the
 // exponential model with float16 rows alike.
-#include <mutex>
-#include <unordered_map>
-
 #pragma once
 
 #include <algorithm>
 
+#include "launch_shape.h"
 #include "march.h"
 
 namespace lq {
@@ -313,25 +311,19 @@ __global__ __launch_bounds__(kBlock) void k_query_multi_plain(
 
 __global__ void k_zero_u64(unsigned long long *p) { p[threadIdx.x * kCounterStride] = 0ull; }
 
-// resident blocks of a kernel on the current device (cached)
-template <class Kern>
-int resident_blocks(Kern kern) {
-    static std::mutex mu;
-    static std::unordered_map<int, int> cache;
+// blocks of a kernel that the current device holds at once
+int resident_blocks(const void *kern) {
+    static ResidentBlocks known;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    std::lock_guard<std::mutex> lk(mu);
-    auto it = cache.find(dev);
-    if (it != cache.end()) return it->second;
-    int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBlock, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 1;
-    (void)hipGetLastError();
-    int nb = per_cu * cus;
-    cache[dev] = nb;
-    return nb;
+    return known.get(dev, kern, [&] {
+        int per_cu = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kBlock, 0) != hipSuccess || per_cu < 1)
+            per_cu = 1;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
+        (void)hipGetLastError();
+        return per_cu * cus;
+    });
 }
 
 // Launch over persistent blocks with ray counters.  kStatic: no counters when
@@ -343,7 +335,7 @@ int resident_blocks(Kern kern) {
 template <bool kStatic, class Kern, class... Args>
 hipError_t launch_persistent(Kern kern, const QueryArgs &a, unsigned long long *queue, hipStream_t s, Args... args) {
     const int64_t need_blocks = (a.n + kBlock - 1) / kBlock;
-    const int64_t nb = std::min<int64_t>(need_blocks, resident_blocks(kern));
+    const int64_t nb = std::min<int64_t>(need_blocks, resident_blocks(reinterpret_cast<const void *>(kern)));
     if (kStatic && nb == need_blocks && !a.n_dev) {
         const int block = a.n <= (int64_t)64 * 1024 ? 64 : kBlock;
         hipLaunchKernelGGL(kern, dim3((unsigned)((a.n + block - 1) / block)), dim3(block), 0, s, args...,

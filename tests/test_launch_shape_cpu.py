@@ -62,3 +62,31 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_resident_blocks_are_a_kernels_own(tmp_path):
+    """Kernels of one signature and of different occupancy, in either order, on
+    two devices; each is asked for once."""
+    _run(tmp_path, r"""
+#include "launch_shape.h"
+#include <cstdio>
+static void a(int) {}
+static void b(int) {}
+int main() {
+    using namespace lq;
+    for (int order = 0; order < 2; ++order) {
+        ResidentBlocks known;
+        int asked = 0;
+        for (int k = 0; k < 6; ++k) {
+            const bool first = (k + order) % 2 == 0;
+            const int device = k / 4, want = (first ? 1280 : 768) + device;
+            const void *kern = reinterpret_cast<const void *>(first ? a : b);
+            const int got = known.get(device, kern, [&] { ++asked; return want; });
+            if (got != want) { std::printf("order %d, call %d: %d\n", order, k, got); return 1; }
+        }
+        if (asked != 4) { std::printf("asked %d times\n", asked); return 1; }
+    }
+    std::printf("ok\n");
+    return 0;
+}
+""")
