@@ -169,21 +169,20 @@ struct SliceScratch {
     SliceScratch(const SliceScratch &) = delete;
 };
 
-// values first .. first + per - 1 of every leaf of t to host memory
-static lq_status download_values(const DevTree &t, int first, int per, float *host) {
+// values first .. first + per - 1 of every leaf of t to host memory, by way of
+// `room` floats of device scratch
+static hipError_t download_values(const DevTree &t, int first, int per, float *scratch, size_t room, float *host) {
     const size_t n = (size_t)t.n_leaves, row_bytes = (size_t)t.row_elems * (t.storage == LQ_F32 ? 4 : 2);
-    const SliceScratch slice(n, (size_t)per * 4);
-    if (!slice.p) return fail(LQ_ERR_OOM, "device scratch of the download");
-    for (size_t at = 0; at < n; at += slice.leaves) {
-        const size_t m = n - at < slice.leaves ? n - at : slice.leaves;
+    hipError_t e = hipSuccess;
+    for (size_t at = 0; at < n && e == hipSuccess; at += room / per) {
+        const size_t m = n - at < room / per ? n - at : room / per;
         hipLaunchKernelGGL(k_unpack_rows, dim3(stream_blocks(m * per)), dim3(kStreamThreads), 0, nullptr,
                            static_cast<const char *>(t.rows) + at * row_bytes, (int64_t)m, first, per, t.row_elems,
-                           t.storage, slice.p);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipMemcpy(host + at * per, slice.p, m * per * 4, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "reading the leaf rows");
+                           t.storage, scratch);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpy(host + at * per, scratch, m * per * 4, hipMemcpyDeviceToHost);
     }
-    return LQ_OK;
+    return e;
 }
 
 // Child table without the leaves for which keep_leaf() is false and without
@@ -265,8 +264,20 @@ lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree *
     t->d_top = nullptr;
     t->d_bricks = nullptr;
     t->d_rows = nullptr;
-    if ((grids && hipMalloc((void **)&t->d_top, top_bytes) != hipSuccess) ||
-        hipMalloc(&t->d_rows, row_total) != hipSuccess) {
+    // an allocation, tried again with the caller's scratch given back
+    bool more_room = (bool)p.make_room;
+    const auto with_room = [&](auto allocate) {
+        hipError_t e = allocate();
+        if (e == hipErrorOutOfMemory && more_room) {
+            (void)hipGetLastError();
+            p.make_room();
+            more_room = false;
+            e = allocate();
+        }
+        return e;
+    };
+    if ((grids && with_room([&] { return hipMalloc((void **)&t->d_top, top_bytes); }) != hipSuccess) ||
+        with_room([&] { return hipMalloc(&t->d_rows, row_total); }) != hipSuccess) {
         (void)hipGetLastError();
         lq_free_octree(t);
         return fail(LQ_ERR_OOM, "device allocation of the tree tables failed");
@@ -300,7 +311,9 @@ lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree *
     size_t brick_bytes = 0;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess)
-        e = build_bricks(t->d_child_skip, p.max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
+        e = with_room([&] {
+            return build_bricks(t->d_child_skip, p.max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
+        });
     if (e == hipErrorOutOfMemory) {   // no room for bricks: the queries march child_skip
         (void)hipGetLastError();
         brick_bytes = 0;
@@ -443,10 +456,13 @@ lq_status lq_octree_download(const lq_octree *t, int32_t *child, float *sigma, f
     const DevTree &dt = t->t;
     if (child && (e = hipMemcpy(child, t->d_child, (size_t)dt.n_nodes * 32, hipMemcpyDeviceToHost)) != hipSuccess)
         return hip_fail(e, "reading the child table");
-    if (dt.n_leaves == 0) return LQ_OK;
-    lq_status st = sigma ? download_values(dt, 0, 1, sigma) : LQ_OK;
-    if (st == LQ_OK && sh) st = download_values(dt, 1, 3 * dt.K, sh);
-    return st;
+    if ((!sigma && !sh) || dt.n_leaves == 0) return LQ_OK;
+    const int per = sh ? 3 * dt.K : 1;
+    const SliceScratch slice((size_t)dt.n_leaves, (size_t)per * 4);
+    if (!slice.p) return fail(LQ_ERR_OOM, "device scratch of the download");
+    if (sigma) e = download_values(dt, 0, 1, slice.p, slice.leaves * per, sigma);
+    if (sh && e == hipSuccess) e = download_values(dt, 1, per, slice.p, slice.leaves * per, sh);
+    return e == hipSuccess ? LQ_OK : hip_fail(e, "reading the leaf rows");
 }
 
 lq_status lq_octree_info(const lq_octree *t, int64_t *device_bytes, int32_t *n_nodes, int32_t *n_leaves,

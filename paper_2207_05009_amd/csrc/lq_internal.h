@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <functional>
 #include <string>
 
 #include "../../include/lumiq.h"
@@ -143,6 +144,7 @@ struct OctreeParts {
     int32_t *child, *child_skip;
     const float *sigma, *sh;
     bool leaves_on_host;
+    std::function<void()> make_room;   // gives device scratch back, called when an allocation fails; or empty
 };
 lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree **out);
 // the scalars of a tree: LQ_OK, or the error a loader returns for them
