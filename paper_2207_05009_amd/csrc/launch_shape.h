@@ -49,4 +49,11 @@ private:
     std::map<std::pair<int, const void *>, int> known_;
 };
 
+// First position of range x when a launch splits n positions into `ranges`
+// (range x ends where x + 1 begins): multiples of `unit`, so that reservations
+// of `unit` positions within a range start on them too.
+constexpr int64_t range_begin(int x, int ranges, int64_t n, int64_t unit) {
+    return x >= ranges ? n : n / unit * x / ranges * unit;
+}
+
 }  // namespace lq

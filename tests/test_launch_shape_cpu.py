@@ -90,3 +90,29 @@ int main() {
     return 0;
 }
 """)
+
+
+def test_camera_reservations_are_whole_tiles(tmp_path):
+    """The ranges of a camera batch, reserved 64 positions at a time: they cover
+    every position once, and each reservation starts on a tile, so that only the
+    last one of the batch holds fewer than 64; and the ranges of other batches."""
+    _run(tmp_path, r"""
+#include "launch_shape.h"
+#include <cstdio>
+int main() {
+    using namespace lq;
+    const int64_t sizes[] = {1, 7, 63, 64, 65, 511, 512, 513, 1283 * 721, 2048 * 2048, 2147483647, (int64_t)1 << 40};
+    for (int64_t n : sizes)
+        for (int64_t unit = 1; unit <= 64; unit += 63) {
+            int64_t at = 0;
+            for (int x = 0; x < 8; ++x) {
+                const int64_t a = range_begin(x, 8, n, unit), b = range_begin(x + 1, 8, n, unit);
+                if (a != at || b < a || a % unit || b - a > n / 8 + 2 * unit) { std::printf("%lld, unit %lld, range %d\n", (long long)n, (long long)unit, x); return 1; }
+                at = b;
+            }
+            if (at != n) { std::printf("%lld ends at %lld\n", (long long)n, (long long)at); return 1; }
+        }
+    std::printf("ok\n");
+    return 0;
+}
+""")
