@@ -319,11 +319,13 @@ __device__ inline void philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, 
 //    centre, m, as a_k |x|^2 + b_k . x + (C_k - m): five FP64 instructions per
 //    blob instead of nine (differences, square, scale, maximum over the blobs,
 //    difference to it).  The host takes this form when no exponent changes by
-//    more than 64 within half a voxel diagonal, so that exp2 neither overflows
-//    nor loses a sample's largest term (the bound keeps the terms themselves,
-//    which cancel in FP64, below 1e5 at depth 10); m is rounded to a whole
-//    number, so 2^m is exact.  Otherwise the maximum is
-//    each sample's own.
+//    more than 7.5 within half a voxel diagonal: the terms that count then stay
+//    below 8, whose rounding to float32 (2^-22) is about exp2's own error, where
+//    an exponent relative to the sample's maximum loses nothing in its largest
+//    terms (two weights at a change of 62, one sample: off by 9.4e-7, 1.2e-7 in
+//    the other form).  Neither does exp2 overflow, and the terms that cancel in
+//    FP64 stay far below 1e5.  m is rounded to a whole number, so 2^m is exact.
+//    Otherwise the maximum is each sample's own.
 //  - Philox: of counter (code, j, 0, 0), round 1's products and one of round
 //    2's depend on the voxel or on j alone: the former are taken once per
 //    voxel, the latter are scalar.
@@ -352,6 +354,7 @@ __device__ inline void philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, 
 // that the loads are not all issued at once.
 constexpr int kBlock = 16;
 constexpr int kProduct = 4;   // DC terms per logarithm
+constexpr double kCentredChange = 7.5;
 
 template <int NB, bool CENTRED, bool PRODUCT>
 __global__ __launch_bounds__(kThreads, NB == 8 ? 5 : NB == 16 ? 4 : 2) void k_distill(const FieldArgs f, const double *__restrict__ rec,
@@ -940,7 +943,7 @@ lq_status lq_distill_leaves(const lq_field_desc *field, int32_t max_depth, float
     const unsigned nb = (unsigned)((total + kThreads - 1) / kThreads);
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     const bool product = dc_products_in_range(f);
-    const bool centred = product && exponent_change(f, max_depth) <= 64.0;
+    const bool centred = product && exponent_change(f, max_depth) <= kCentredChange;
     const int NB = f.nb <= 8 ? 8 : f.nb <= 16 ? 16 : 32;
     std::vector<unsigned char> rec = blob_records(field, f, NB, centred);
     double *d_rec;
