@@ -332,10 +332,10 @@ __device__ inline void philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, 
 //  - Only the shells that a voxel of the wave can touch are tested.
 //  - PRODUCT: the logarithms of up to four samples' DC terms are taken of
 //    their product (three roundings of 2^-24 instead of three logarithms'
-//    errors); the host takes this form when the products stay within range
-//    and no radiance is close to L_max.  Otherwise each term has its own
-//    logarithm, and L_max - E, which would cancel, is summed from the blobs'
-//    L_max - e_k.
+//    errors); the host takes this form when the products stay within range and
+//    no radiance is above L_max / 2.  Otherwise each term has its own logarithm,
+//    and L_max - E, which would cancel, is summed from the blobs' L_max - e_k
+//    (one blob at L_max (1 - 2^-10): DC off by 4e-4 in the first form).
 // 256^3, 882k voxels kept, 256 samples, 16 blobs, 4 shells: 1.99 ms (2.95 ms
 // with nine FP64 instructions per blob, all shells tested, a logarithm per
 // sample and the radiance sums sunk below the shell loop); VALU busy 97 %.
@@ -490,9 +490,9 @@ __global__ __launch_bounds__(kThreads, NB == 8 ? 5 : NB == 16 ? 4 : 2) void k_di
             // DC: logit(E / L_max) / Y_00 = ln(E / (L_max - E)) 2 sqrt(pi),
             // E = e_c / s
             if constexpr (PRODUCT) {
-                const float E0 = e0 * inv, E1 = e1 * inv, E2 = e2 * inv;
-                n0 *= E0, n1 *= E1, n2 *= E2;
-                d0 *= f.l_max - E0, d1 *= f.l_max - E1, d2 *= f.l_max - E2;
+                // both through the same rounded 1 / s, which so cancels
+                n0 *= e0 * inv, n1 *= e1 * inv, n2 *= e2 * inv;
+                d0 *= fmaf(f.l_max, s, -e0) * inv, d1 *= fmaf(f.l_max, s, -e1) * inv, d2 *= fmaf(f.l_max, s, -e2) * inv;
                 if ((j & (kProduct - 1)) == kProduct - 1 || j + 1 == j1) {
                     dc0 = fmaf(__builtin_amdgcn_logf(n0 * __builtin_amdgcn_rcpf(d0)), kLn2InvY00, dc0);
                     dc1 = fmaf(__builtin_amdgcn_logf(n1 * __builtin_amdgcn_rcpf(d1)), kLn2InvY00, dc1);
@@ -846,16 +846,16 @@ double exponent_change(const FieldArgs &f, int depth) {
 }
 
 // Whether products of four factors E, of four factors L_max - E and of their
-// quotients stay within 2^-100 .. 2^100; E, a mean of the blobs' radiances,
-// lies between them (quotients between 2^-24 and 2^12).
+// quotients stay within 2^-100 .. 2^100, and L_max - E cancels no more than a
+// bit; E, a mean of the blobs' radiances, lies between them (quotients between
+// 2^-24 and 1).
 bool dc_products_in_range(const FieldArgs &f) {
     float lo = f.l_max, hi = 0.0f;
     for (int k = 0; k < f.nb; ++k) {
         lo = std::min({lo, f.er[k], f.eg[k], f.eb[k]});
         hi = std::max({hi, f.er[k], f.eg[k], f.eb[k]});
     }
-    return lo > 0x1p-24f * std::max(1.0f, f.l_max) && f.l_max < 0x1p24f &&
-           f.l_max - hi > std::max(0x1p-24f, 0x1p-12f * f.l_max);
+    return lo > 0x1p-24f * std::max(1.0f, f.l_max) && f.l_max < 0x1p24f && f.l_max > 0x1p-23f && hi <= 0.5f * f.l_max;
 }
 
 // The sample loop's blob records (layout at k_distill), as bytes.  Those past

@@ -51,3 +51,25 @@ def test_weights_are_as_precise_as_their_exponentials(change):
     # ln density = sum a g: 24 times a term's error, the argument of exp2 (below 32), exp2
     log_err = np.abs(sig / ref_sig - 1.0).max()
     assert log_err <= 24.0 * (eps + 3 * U) + 2.0 ** -20 * np.log(2.0) + 2 * U, log_err
+
+
+@pytest.mark.parametrize("bright", [0.05, 0.45, 0.499, 0.501, 0.9, 1.0 - 2.0 ** -10, 1.0 - 2.0 ** -14])
+def test_dc_near_the_ceiling(bright):
+    """One blob of radiance bright * l_max: the DC coefficient is a constant,
+    2 sqrt(pi) ln(E / (l_max - E)).  Up to half the ceiling the difference is taken
+    of rounded sums (a rounding of E times E / (l_max - E)); above, from the blobs'
+    own differences, which cancel nothing."""
+    depth = 4
+    p = field_params(inputs.TreeSpec(depth=depth, n_blobs=1, n_shells=0, sh_degree=1, seed=5, occupancy=0.3))
+    p["radii"] = np.array([0.4])
+    p["emission"] = np.float32(bright * p["l_max"]) * np.ones((1, 3))
+    print(f"[gpu] distillation, radiance at {bright} of the ceiling", flush=True)
+    _, sh, _, ref = _distilled(p, depth, 1, 9)
+    ratio = float(p["emission"][0, 0] / (p["l_max"] - p["emission"][0, 0]))
+    # the quotient: E, the difference, their products, rcp (one ulp); log2 (one ulp), the scaled result
+    amplified = ratio if bright <= 0.5 else 0.0
+    scale = 2.0 * np.sqrt(np.pi)
+    bound = scale * (amplified + 8.0) * U + scale * np.log(2.0) * 2 * U * max(1.0, abs(np.log2(ratio))) + 2 * U * scale * abs(np.log(ratio))
+    err = np.abs(sh[:, :, 0] - ref[:, :, 0]).max()
+    print(f"[gpu] DC off by {err:.2e}, bound {bound:.2e}", flush=True)
+    assert err <= bound
