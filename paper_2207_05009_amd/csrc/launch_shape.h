@@ -9,11 +9,12 @@
 
 namespace lq {
 
-// Blocks of kStreamThreads for a kernel that strides over n items.  HIP takes
-// fewer than 2^32 threads in a dimension, and the largest trees hold more words
-// (a float32 leaf of SH degree 4 has 128, so 2^25 leaves are beyond it): at most
-// kStreamBlocks, each thread then taking several items.  All tables up to 2^30
-// words keep a thread per word.
+// Blocks of kStreamThreads for a kernel that strides over n items.  A launch of
+// 2^32 threads or more in a dimension is not refused: the count wraps and the
+// rest of the items is left out.  The largest trees hold that many words (a
+// float32 leaf of SH degree 4 has 128, so 2^25 leaves do): at most kStreamBlocks,
+// each thread then taking several items.  All tables up to 2^30 words keep a
+// thread per word.
 constexpr unsigned kStreamThreads = 256;
 constexpr unsigned kStreamBlocks = 1u << 22;
 inline unsigned stream_blocks(uint64_t n) {
