@@ -513,6 +513,8 @@ __global__ __launch_bounds__(kThreads, NB == 8 ? 5 : NB == 16 ? 4 : 2) void k_di
         dc2_sum += (double)dc2;
     }
     if (!mine) return;
+    // no ceiling: ln(E / infinity), where inf * 0 has entered the sums of L_max - e_k
+    if (!PRODUCT && isinf(f.l_max)) dc0_sum = dc1_sum = dc2_sum = -INFINITY;
     const double invn = 1.0 / (double)n_samples;
     sigma_out[i] = (float)(sig_sum * invn);
     const int K = f.K;

@@ -73,3 +73,18 @@ def test_dc_near_the_ceiling(bright):
     err = np.abs(sh[:, :, 0] - ref[:, :, 0]).max()
     print(f"[gpu] DC off by {err:.2e}, bound {bound:.2e}", flush=True)
     assert err <= bound
+
+
+def test_infinite_ceiling():
+    """E / l_max is 0 for an infinite l_max: every DC coefficient is -inf, also
+    where a blob's weight vanishes."""
+    import torch
+    from paper_2207_05009_amd import lumiq
+    p = field_params(inputs.TreeSpec(depth=4, n_blobs=6, n_shells=2, sh_degree=1, seed=6, occupancy=0.3))
+    p["radii"] = np.full(6, 0.02)
+    p["l_max"] = np.inf
+    print("[gpu] distillation without a ceiling", flush=True)
+    _, sig, sh = lumiq.distill_leaves(p, 4, 0.01, 20, 3)
+    torch.cuda.synchronize()
+    assert len(sig) > 0 and bool(torch.isfinite(sig).all()) and bool(torch.isfinite(sh[:, :, 1:]).all())
+    assert bool((sh[:, :, 0] == -np.inf).all())
