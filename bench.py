@@ -9,9 +9,10 @@ with a 40 degree field of view; linear transmittance, sigma_min = 0.1,
 alpha_max = 0.9.
 
 Prints one JSON line (rays/s) with the dominant kernel's roofline fraction
-(algorithmic bytes per launch / measured launch time vs 8 TB/s; the bytes
-are counted on the table the timed kernel marches) and the CPU oracle's
-throughput on a bounded sample of the same rays.  Extra variants
+(the bytes every launch has to move -- rays in, results out -- per measured
+launch time, vs 8 TB/s, beside the HBM bytes of the committed counter
+summary), the work of the octree march that defines the query per second, and
+the CPU oracle's throughput on a bounded sample of the same rays.  Extra variants
 (float16/bfloat16 storage, exponential transmittance, incoherent room
 queries, the learned surrogate with octree fallback, the consumer side, the
 uneven 16-luminaire batch) are reported under "variants".
@@ -70,44 +71,45 @@ def time_launches(fn, steps, warmup):
     return start.elapsed_time(end) / steps, wall
 
 
-def alg_bytes(trace, K, elem_bytes):
-    """Bytes the method must move per launch, counted on the table the
-    production query marches (a trace with LQ_TRACE_PRUNED: only the leaves
-    it composites, the nodes of that table it visits): rays in (24 B), RGB +
-    alpha out (16 B), per composited leaf its density and 3K SH coefficients,
-    one 4-byte child slot per octree node visited."""
+def query_bytes(n):
+    """Bytes a query launch cannot do without: rays in (24 B), RGB + alpha out
+    (16 B).  What it reads of the tables depends on the march and the caches."""
+    return 40 * n
+
+
+def octree_work(trace, K, elem_bytes, ms):
+    """The octree march's work, per second of the timed launch: rays in, RGB +
+    alpha out, per composited leaf its density and 3K SH coefficients, one 4-byte
+    child slot per node visited, counted by a trace of the sigma_min-pruned table
+    (LQ_TRACE_PRUNED).  The timed kernel reaches the same leaves over brick tables,
+    in fewer steps and with other reads, and its caches serve most of them: a
+    measure of work, not of bandwidth, and no part of a roofline fraction."""
     n = trace["count"].numel()
     comp = int(trace["n_comp"].sum())
     steps = int(trace["n_steps"].sum())
-    return 40 * n + comp * (1 + 3 * K) * elem_bytes + steps * 4, {
-        "rays": n, "mean_composited": comp / n, "mean_nodes": steps / n}
+    nbytes = query_bytes(n) + comp * (1 + 3 * K) * elem_bytes + steps * 4
+    return {"bytes_per_launch": nbytes, "gb_per_s": round(nbytes / (ms * 1e-3) / 1e9, 1),
+            "per_ray": {"rays": n, "mean_composited": comp / n, "mean_octree_nodes": steps / n}}
 
 
-def alg_bytes_full_table(trace, K, elem_bytes):
-    """The same formula on the full table (the validation trace): a density
-    per data leaf visited, including those below sigma_min that the
-    production query never reads, and the nodes of the full table."""
-    n = trace["count"].numel()
-    occ = int(trace["count"].sum())
-    comp = int(trace["n_comp"].sum())
-    steps = int(trace["n_steps"].sum())
-    return 40 * n + occ * elem_bytes + comp * 3 * K * elem_bytes + steps * 4, {
-        "rays": n, "mean_leaves": occ / n, "mean_composited": comp / n, "mean_nodes": steps / n}
+def roofline_record(n, ms, traffic):
+    """A query launch against HBM: the bytes it cannot do without, and those it
+    moves as measured (null without a counter summary of the current sources)."""
+    gbs = query_bytes(n) / (ms * 1e-3) / 1e9
+    rec = {"bytes_per_launch": query_bytes(n), "achieved_gbs": round(gbs, 1), "roofline_frac": round(gbs / HBM_PEAK_GBS, 4),
+           "traffic": traffic, "traffic_frac": None}
+    if traffic is not None:
+        rec["traffic_frac"] = round(traffic / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
+    return rec
 
 
 def variant_record(lumiq, oc, o, d, model, K, elem_bytes, vms, traffic_tag=None):
-    """rays/s of a timed query launch and its algorithmic bytes against the
-    HBM peak (per-ray counts from a trace of the pruned table over the same
-    rays), plus the measured HBM bytes per launch where a counter summary
-    exists."""
+    """rays/s of a timed query launch, its bytes against the HBM peak and the
+    octree march's work over the same rays."""
     n = o.shape[0]
-    nbytes, counts = alg_bytes(oc.trace(o, d, model=model, flags=lumiq.LQ_TRACE_PRUNED), K, elem_bytes)
-    achieved = nbytes / (vms * 1e-3) / 1e9
-    rec = {"rays_per_s": n / (vms * 1e-3), "ms_per_step": vms, "alg_bytes_per_launch": nbytes,
-           "achieved_gbs": round(achieved, 1), "roofline_frac": round(achieved / HBM_PEAK_GBS, 4),
-           "per_ray": counts}
-    if traffic_tag:
-        rec["traffic"] = traffic_from_profiles(traffic_tag)
+    rec = {"rays_per_s": n / (vms * 1e-3), "ms_per_step": vms}
+    rec.update(roofline_record(n, vms, traffic_from_profiles(traffic_tag) if traffic_tag else None))
+    rec["octree_work"] = octree_work(oc.trace(o, d, model=model, flags=lumiq.LQ_TRACE_PRUNED), K, elem_bytes, vms)
     return rec
 
 
@@ -794,21 +796,13 @@ def main():
 
     samples = {}
     keep_sample(samples, "headline", rgb, alpha, sample_index(n, 11), tree="c1", rays="camera")
-    trp = oct32.trace(o, d, model="linear", flags=lumiq.LQ_TRACE_PRUNED)
-    tr = oct32.trace(o, d, model="linear")
+    work = octree_work(oct32.trace(o, d, model="linear", flags=lumiq.LQ_TRACE_PRUNED), tree.K, 4, ms)
     torch.cuda.synchronize()
-    nbytes, counts = alg_bytes(trp, tree.K, 4)
-    full_bytes, full_counts = alg_bytes_full_table(tr, tree.K, 4)
-    del trp, tr
-    achieved = nbytes / (ms * 1e-3) / 1e9
-    traffic = traffic_from_profiles("query_f32_camera")
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "alg_bytes_per_launch": nbytes, "per_ray": counts,
-                "full_table": {"alg_bytes_per_launch": full_bytes, "per_ray": full_counts,
-                               "frac": round(full_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                               "note": "counts of the validation trace over the full table (densities of "
-                                       "leaves below sigma_min and nodes the timed kernel never visits)"},
+    rec = roofline_record(n, ms, traffic_from_profiles("query_f32_camera"))
+    roofline = {"against": "hbm", "achieved": rec["achieved_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": rec["roofline_frac"], "bytes_per_launch": rec["bytes_per_launch"], "traffic": rec["traffic"],
+                "traffic_frac": rec["traffic_frac"], "octree_work": work,
+                "bound": "vector issue and dependent loads, far from memory (profiles/query_valu_counters.md)",
                 "kernel": "k_query_plain<F32, SH deg 2, brick tables of the sigma_min-pruned tree, linear, 8x8 pixel tiles>",
                 "kernel_sources": kernel_sources_hash()}
 
