@@ -133,7 +133,8 @@ lq_status lq_query_radiance(const lq_octree *tree, const float *origins, const f
  * errors as lq_query_radiance.  The launch's only scratch -- 8 ray
  * counters, 2 KB, whatever n -- lives in a static device array of the
  * library (one copy per GPU, held until the process ends), cleared by a
- * kernel at the start of every call.  Every call on one GPU shares that
+ * kernel at the start of a call that uses it (a batch that fits the GPU at
+ * once does without).  Every call on one GPU shares that
  * array: calls that overlap in time on one GPU (concurrent streams, or
  * threads) race on it and give wrong results; serialise them.  Its address
  * is looked up on the first call on each device.
@@ -173,13 +174,17 @@ lq_status lq_query_radiance_image(const lq_octree *tree, const float *origins, c
  *                nodes, each reached by one descent), up to the stop;
  *   leaf_ids     optional [n][max_ids]: the first max_ids leaf ids.
  * rgb/alpha may be NULL.  All arrays are device pointers.
- * With LQ_TRACE_PRUNED the trace marches the table that lq_query_radiance
- * marches: the tree without the data leaves whose stored density is below
- * sigma_min and without the nodes they leave empty (Sec. 6.2: those leaves
- * are never composited).  Radiance and alpha are those the production
- * query computes; the records then list only the composited leaves (count
- * = n_comp) and n_steps counts the nodes of that table visited -- the work
- * of the production query.  It combines with LQ_NO_EARLY_TERM only.
+ * The trace walks the octree node by node.  lq_query_radiance reaches the
+ * same leaves over the same segments through brick tables, in other steps; a
+ * segment that starts at an edge or a corner of the grid may be rounded
+ * through another axis there (the last bits of that segment's length).
+ * With LQ_TRACE_PRUNED the trace walks the tree whose leaves
+ * lq_query_radiance reaches: without the data leaves whose stored density is
+ * below sigma_min and without the nodes they leave empty (Sec. 6.2: those
+ * leaves are never composited).  The records then list only the composited
+ * leaves (count = n_comp) and n_steps counts the nodes of that tree visited:
+ * the query's work as an octree march, more than its steps over bricks.
+ * It combines with LQ_NO_EARLY_TERM only.
  */
 lq_status lq_query_trace(const lq_octree *tree, const float *origins, const float *dirs,
                          int64_t n, float *rgb, float *alpha, int model, uint32_t flags,
