@@ -9,8 +9,8 @@
 //                   512-bit occupancy mask;
 //   k_top_extents, k_brick_extents  the empty extents, from the bit rows.
 // Each pass streams its tables once; the extents take whole rows of cells as
-// bits (row_codes).  All of it: 0.27 ms for a depth-8 luminaire of 882k leaves,
-// 0.7 ms at depth 9, 3.2 ms at depth 10.
+// bits (row_codes).  All kernels of it: 0.12 ms for a depth-8 luminaire of 882k
+// leaves, 0.31 ms at depth 9 (6.2M), 1.27 ms at depth 10 (46M).
 #include <hip/hip_runtime.h>
 
 #include "lq_internal.h"
@@ -112,9 +112,9 @@ __global__ __launch_bounds__(kBrickCells) void k_brick_fill(const int32_t *child
 // the rows of the m x m square that the cubes of m cells cover are ORed, the
 // cells along x ORed by shifts; a cell whose bit stays clear has an empty cube.
 // The codes are counted in three bit planes (the cubes are nested).  A wave takes
-// rows of one octant, so its loops are uniform.  All brick tables of a
-// depth-8, 9 and 10 luminaire: 0.27, 0.71 and 3.2 ms; 3.2, 9.7 and 42.7 ms with
-// the cubes tested cell by cell, a lane per cell.
+// rows of one octant, so its loops are uniform.  Both extent kernels of a
+// depth-8, 9 and 10 luminaire: 0.09, 0.25 and 1.01 ms; tested cell by cell, a lane
+// per cell, the tables took 3.2, 9.7 and 42.7 ms.
 struct Bits128 {
     unsigned long long lo, hi;
 };
