@@ -336,7 +336,7 @@ __device__ inline void philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, 
 //    no radiance is above L_max / 2.  Otherwise each term has its own logarithm,
 //    and L_max - E, which would cancel, is summed from the blobs' L_max - e_k
 //    (one blob at L_max (1 - 2^-10): DC off by 4e-4 in the first form).
-// 256^3, 882k voxels kept, 256 samples, 16 blobs, 4 shells: 1.99 ms (2.95 ms
+// 256^3, 882k voxels kept, 256 samples, 16 blobs, 4 shells: 2.0 ms (2.95 ms
 // with nine FP64 instructions per blob, all shells tested, a logarithm per
 // sample and the radiance sums sunk below the shell loop); VALU busy 97 %.
 // (Taking the exponents and the sums over the blobs to the matrix cores, a

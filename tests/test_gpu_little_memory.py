@@ -21,11 +21,16 @@ class Filled:
         import torch
         torch.cuda.synchronize()
         torch.cuda.empty_cache()
-        self.held = []
-        while torch.cuda.mem_get_info()[0] > self.free + 4 * MB:
+        self.held, piece = [], 16 << 30
+        while piece >= 2 * MB:
             left = torch.cuda.mem_get_info()[0] - self.free
-            self.held.append(torch.empty(min(left, 16 << 30) // (2 * MB) * 2 * MB or 2 * MB, dtype=torch.uint8,
-                                         device="cuda"))
+            if left < piece:
+                piece //= 2
+                continue
+            try:
+                self.held.append(torch.empty(piece, dtype=torch.uint8, device="cuda"))
+            except torch.cuda.OutOfMemoryError:
+                piece //= 2
         print(f"[gpu] {torch.cuda.mem_get_info()[0] / MB:.0f} MB of the card left", flush=True)
         return self
 
