@@ -97,6 +97,10 @@ typedef struct {
  * sigma and sh arrays, little-endian).  storage selects the device precision
  * of sigma and SH (FP32 values are rounded to nearest-even).  The tree is
  * uploaded to `device`, which becomes current for the calling thread.
+ * Device memory beside the tree's own tables: up to 64 MiB during the call.
+ * Where the device has no room for the tables that the plain queries march
+ * (2 KB per 8^3 cells that hold a leaf), the tree is kept without them and
+ * answers the same, more slowly.
  * Errors: LQ_ERR_INVALID_ARG, LQ_ERR_FORMAT (structure check failed),
  * LQ_ERR_IO, LQ_ERR_OOM, LQ_ERR_HIP.  *out is NULL on failure.
  */
@@ -387,7 +391,8 @@ lq_status lq_octree_from_leaves(int32_t max_depth, int32_t sh_degree, const uint
  * Copy a tree's tables to host memory: child [n_nodes][8], sigma [n_leaves]
  * and sh [n_leaves][3][K] (any may be NULL), with the sizes lq_octree_info
  * reports; values as stored (float16 / bfloat16 widened exactly to
- * float32).  Synchronous.
+ * float32).  Device scratch: up to 64 MiB, less where there is less.
+ * Synchronous.
  */
 lq_status lq_octree_download(const lq_octree *tree, int32_t *child, float *sigma, float *sh);
 

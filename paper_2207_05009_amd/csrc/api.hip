@@ -310,14 +310,15 @@ lq_status make_octree(const OctreeParts &p, int storage, int device, lq_octree *
     dt.alpha_max = p.alpha_max;
     size_t brick_bytes = 0;
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess)
+    if (e == hipSuccess) {
         e = with_room([&] {
             return build_bricks(t->d_child_skip, p.max_depth, &t->d_bricks, &brick_bytes, &dt.brick_top, &dt.bricks);
         });
-    if (e == hipErrorOutOfMemory) {   // no room for bricks: the queries march child_skip
-        (void)hipGetLastError();
-        brick_bytes = 0;
-        e = hipSuccess;
+        if (e == hipErrorOutOfMemory) {   // no room for bricks: the queries march child_skip
+            (void)hipGetLastError();
+            brick_bytes = 0;
+            e = hipSuccess;
+        }
     }
     if (e != hipSuccess) {
         lq_free_octree(t);
@@ -353,6 +354,7 @@ lq_status lq_load_octree_desc(const lq_octree_desc *desc, int storage, int devic
     }
     if (device < 0 || device >= ndev) return fail(LQ_ERR_INVALID_ARG, "device index out of range");
     if ((e = hipSetDevice(device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
+    (void)hipGetLastError();   // what an earlier call of the program left is not this call's
 
     const std::vector<int32_t> skip = prune_tree(desc, bfs, [&](int64_t leaf) {
         // density as stored (after rounding), compared like the kernel does
@@ -453,6 +455,7 @@ lq_status lq_octree_download(const lq_octree *t, int32_t *child, float *sigma, f
     if (!t) return fail(LQ_ERR_INVALID_ARG, "tree is NULL");
     hipError_t e = hipSetDevice(t->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
+    (void)hipGetLastError();   // as in the loader
     const DevTree &dt = t->t;
     if (child && (e = hipMemcpy(child, t->d_child, (size_t)dt.n_nodes * 32, hipMemcpyDeviceToHost)) != hipSuccess)
         return hip_fail(e, "reading the child table");

@@ -988,6 +988,7 @@ lq_status lq_octree_from_leaves(int32_t max_depth, int32_t sh_degree, const uint
         if ((st = check_device_array(sigma, (size_t)n_leaves * 4, device, "sigma")) != LQ_OK) return st;
         if ((st = check_device_array(sh, (size_t)n_leaves * 12 * K, device, "sh")) != LQ_OK) return st;
     }
+    (void)hipGetLastError();   // what an earlier call of the program left is not this call's
     hipStream_t s = nullptr;
     DevBufs b;
     const uint64_t n = (uint64_t)n_leaves;
